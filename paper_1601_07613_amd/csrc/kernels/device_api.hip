@@ -758,10 +758,27 @@ dgc_status dgc_permute_records(const void *src, void *dst, const int32_t *perm, 
     if (!src || !dst || !perm || n_rec < 0 || rec_bytes <= 0 || rec_bytes % 4 != 0 || src == dst)
         return fail(DGC_E_ARG, "dgc_permute_records: bad argument");
     if (n_rec == 0) return DGC_OK;
-    const int64_t words = rec_bytes / 4;
-    hipLaunchKernelGGL(dgc_dev::permute_records_kernel, dim3(grid_for(n_rec * words)), dim3(kBlock), 0,
-                       static_cast<hipStream_t>(stream), static_cast<const uint32_t *>(src), static_cast<uint32_t *>(dst),
-                       perm, n_rec, words, to_layout ? 1 : 0);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    // the widest piece that the record size and both buffers' alignment allow
+    const uintptr_t al = reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst) | (uintptr_t)rec_bytes;
+    auto go = [&](auto piece) {
+        using V = decltype(piece);
+        const int64_t words = rec_bytes / (int64_t)sizeof(V);
+        const int64_t per_block = kBlock * dgc_dev::kPermutePieces;
+        const dim3 grid((unsigned)((n_rec * words + per_block - 1) / per_block));
+        // 32-bit indices as long as the last work-group's stay below 2^32
+        if (n_rec * words <= (int64_t)UINT32_MAX - per_block)
+            hipLaunchKernelGGL((dgc_dev::permute_records_kernel<V, uint32_t>), grid, dim3(kBlock), 0, st,
+                               static_cast<const V *>(src), static_cast<V *>(dst), perm, (uint32_t)n_rec,
+                               (uint32_t)words, to_layout ? 1 : 0);
+        else
+            hipLaunchKernelGGL((dgc_dev::permute_records_kernel<V, int64_t>), grid, dim3(kBlock), 0, st,
+                               static_cast<const V *>(src), static_cast<V *>(dst), perm, n_rec, words,
+                               to_layout ? 1 : 0);
+    };
+    if (al % 16 == 0) go(uint4{});
+    else if (al % 8 == 0) go(uint2{});
+    else go(uint32_t{});
     return hip_check("permute kernel launch");
 }
 

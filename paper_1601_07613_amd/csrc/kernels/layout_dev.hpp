@@ -1,8 +1,7 @@
 // Device helpers of the layout and of the refinement map.
 //
 // permute_records: gather / scatter of element records between the caller's
-// element order and the layout order of Section 5 (one work-item per 4-byte
-// word of a record).
+// element order and the layout order of Section 5.
 // child_colors: the closed-form coloring of a 4-way split (Section 3.2):
 // the first / second child of a parent edge of color c get c / (c + 3) mod 6
 // and each interior edge the color of the parallel parent edge; one
@@ -16,19 +15,47 @@
 
 namespace dgc_dev {
 
-__global__ __launch_bounds__(256) void permute_records_kernel(const uint32_t *__restrict__ src,
-                                                              uint32_t *__restrict__ dst,
-                                                              const int32_t *__restrict__ perm, int64_t n_rec,
-                                                              int64_t words, int to_layout) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n_rec * words) return;
-    const int64_t i = t / words, w = t % words;
-    const int64_t j = perm[i];
-    if (j < 0 || j >= n_rec) return;
-    if (to_layout)
-        dst[j * words + w] = src[i * words + w];
-    else
-        dst[i * words + w] = src[j * words + w];
+// Pieces of V bytes (16, 8 or 4: the widest that the record size and both
+// buffers' alignment allow), kPermutePieces per work-item, a work-group's
+// pieces interleaved so that consecutive lanes move consecutive pieces.
+// Bound by memory: two record passes, one of them scattered by record.
+// Measured into / out of the layout order: 991,232 records of 192 bytes
+// 92 / 70 us (4.1 / 5.4 TB/s), 65,522 of 320 bytes 6.7 / 7.3 us.  With one
+// 4-byte word per work-item and 64-bit index divisions 164 / 166 and
+// 14.2 / 15.0 us; with the reads under a branch per piece, which serialises
+// them, 98 / 82 and 20.2 / 20.2 us; 1, 2 or 8 pieces are within 5 %.
+constexpr int kPermutePieces = 4;
+template <class V, class I>
+__global__ __launch_bounds__(256) void permute_records_kernel(const V *__restrict__ src, V *__restrict__ dst,
+                                                              const int32_t *__restrict__ perm, I n_rec, I words,
+                                                              int to_layout) {
+    const I n = n_rec * words;
+    const I t0 = (I)blockIdx.x * (256 * kPermutePieces) + threadIdx.x;
+    // every read is unconditional (of piece n - 1 or record 0 where there is
+    // nothing to move), so that all of a work-item's reads are in flight at once
+    I rec[kPermutePieces], word[kPermutePieces];
+    int32_t p[kPermutePieces];
+#pragma unroll
+    for (int u = 0; u < kPermutePieces; ++u) {
+        const I t = t0 + (I)(u * 256);
+        const I c = t < n ? t : n - 1;
+        rec[u] = c / words;
+        word[u] = c - rec[u] * words;
+        p[u] = perm[rec[u]];
+    }
+    V v[kPermutePieces];
+    I to[kPermutePieces];
+    bool ok[kPermutePieces];
+#pragma unroll
+    for (int u = 0; u < kPermutePieces; ++u) {
+        ok[u] = t0 + (I)(u * 256) < n && p[u] >= 0 && (I)p[u] < n_rec;
+        const I o = (ok[u] ? (I)p[u] : (I)0) * words + word[u], i = rec[u] * words + word[u];
+        to[u] = to_layout ? o : i;
+        v[u] = src[to_layout ? i : o];
+    }
+#pragma unroll
+    for (int u = 0; u < kPermutePieces; ++u)
+        if (ok[u]) dst[to[u]] = v[u];
 }
 
 __global__ __launch_bounds__(256) void child_colors_kernel(const int8_t *__restrict__ parent, int64_t n,
