@@ -295,7 +295,8 @@ typedef struct {
     const uint8_t *face_code;  /* [2][n_face] */
     const double *face_geo;    /* [dim+3][n_face] */
     const double *elem_geo;    /* [dim*dim+1][n_elem] */
-    const int32_t *elem_slots; /* [max_slots][n_elem] (GATHER only; may be NULL otherwise) */
+    const int32_t *elem_slots; /* [max_slots][n_elem] (GATHER, COMPACT and the one-pass RK
+                                  stage; may be NULL otherwise) */
     const double *tables;      /* dgc_tables layout for (elem_type, p) */
     /* launch tuning (0 = library default); any valid choice gives the same
      * result up to the rounding of the accumulation order */
@@ -328,15 +329,22 @@ typedef struct {
  * per stage; the volume term is then computed by the face team (lane =
  * variable, or lane = mode for tetrahedra at p = 1) whatever vol_form says.
  * Where its conditions fail it falls back to DGC_RK_FUSED.
- * DGC_RK_DEFAULT is DGC_RK_FUSED_VOLUME for triangles at p <= 3, for
+ * DGC_RK_DEFAULT, with vol_form DGC_VOL_DEFAULT, evaluates each stage in one
+ * pass over the elements where it can: every element evaluates its volume
+ * term and the fluxes of all its faces (both elements of a face evaluate it,
+ * each keeping its own side) and writes the stage combination of its own
+ * record, so the right-hand side is never stored and one launch covers the
+ * mesh.  It needs elem_slots (it runs without them as below) and at most 6
+ * face slots per triangle; in f32 it is taken where it rounds exactly as the
+ * colored launches do: conforming triangles at p <= 3 and parallelograms
+ * colored with as many colors as an element has faces, and mixed meshes.
+ * Otherwise DGC_RK_DEFAULT is DGC_RK_FUSED_VOLUME for triangles at p <= 3, for
  * quadrilaterals (f32 only at p = 3) and for f64 tetrahedra at p = 1 when
- * vol_form is DGC_VOL_DEFAULT (measured 2-18 % faster per step on ~1M
- * elements), and
- * DGC_RK_FUSED otherwise (triangles at p = 4, 5: the face kernel's
- * registers run out; f32 tetrahedra: no gain, the face team evaluates the
- * flux of the volume term on each of its four lanes), except for
- * tetrahedra at p = 2, where the combination stays a kernel of its own (the
- * combining team kernel runs out of registers). */
+ * vol_form is DGC_VOL_DEFAULT, and DGC_RK_FUSED otherwise (triangles at
+ * p = 4, 5: the face kernel's registers run out; f32 tetrahedra: no gain, the
+ * face team evaluates the flux of the volume term on each of its four lanes),
+ * except for tetrahedra at p = 2, where the combination stays a kernel of its
+ * own (the combining team kernel runs out of registers). */
 enum { DGC_RK_DEFAULT = 0, DGC_RK_SEPARATE = 1, DGC_RK_FUSED = 2, DGC_RK_BLOCK = 3, DGC_RK_FUSED_VOLUME = 4 };
 
 /* Volume-kernel forms: DGC_VOL_VALU evaluates each element in one work-item
@@ -405,14 +413,16 @@ dgc_status dgc_surface_rhs(const dgc_dmesh *dm, const void *U, void *rhs, int32_
 
 /* One SSP-RK3 step (Shu-Osher form) of U (device f64, updated in place):
  * three stages of volume term + surface term (`variant`) + combination,
- * launched as dm->rk_form says (the volume term and the combination may
- * ride on the first and last color's face kernels, see DGC_RK_*).  With
+ * launched as dm->rk_form says (one pass over the elements per stage, or the
+ * volume term and the combination riding on the first and last color's face
+ * kernels, see DGC_RK_*).  With
  * DGC_SURF_COMPACT in f64 on conforming triangle and parallelogram meshes
  * (any rk_form but DGC_RK_SEPARATE) a stage is two launches: the face pass, then one element
  * pass that evaluates the volume term (the team form, whatever vol_form
  * says), adds the face records and writes the stage combination.
- * DGC_F32 evaluates both terms on an f32 shadow of the stage state and
- * accumulates the stages in f64.  ws holds the stage states and the RHS
+ * DGC_F32 evaluates both terms on the stage state rounded to f32 (the
+ * colored launches through an f32 shadow) and accumulates the stages in f64.
+ * ws holds the stage states and the RHS
  * (DGC_WS_RK_STEP bytes, dgc_rk_workspace_layout).  Errors: DGC_E_ARG,
  * DGC_E_NOT_COLORED, DGC_E_WORKSPACE, DGC_E_UNSUPPORTED, DGC_E_HIP. */
 dgc_status dgc_rk_step(const dgc_dmesh *dm, double *U, double dt, int32_t variant, int32_t precision,
@@ -516,7 +526,8 @@ dgc_status dgc_volume_rhs_batched(const void *host_desc, const void *dev_desc, i
 /* One SSP-RK3 step of every mesh of the batch with its own dt: a fixed
  * sequence of launches (plus one for the f32 shadow), independent of the
  * number of meshes, so it can be captured once in a graph and replayed.
- * When every member has exactly one face of each color (conforming meshes
+ * When every member can run the one-pass element stage (see DGC_RK_DEFAULT)
+ * a step is three launches.  Otherwise, when every member has exactly one face of each color (conforming meshes
  * colored with as many colors as an element has faces), each stage is one
  * launch per color, the first also evaluating the volume term where the
  * single-mesh DGC_RK_DEFAULT step does (triangles p <= 3, quadrilaterals,

@@ -201,10 +201,12 @@ class DeviceMesh:
         fused into the first color's face kernel ("fused_volume"); the
         combination as a separate kernel ("separate"); or the whole step in
         one work-group ("block", an alternative for small meshes, measured
-        slower).  "default" is "fused_volume" for triangles at p <= 3,
-        quadrilaterals (f32 only at p = 3) and f64 tetrahedra at p = 1 (with
-        the default volume form), else "fused" (tetrahedra at p = 2:
-        "separate")."""
+        slower).  "default" evaluates each stage in one pass over the elements
+        (needs the element slots and the default volume form; in f32
+        conforming triangles at p <= 3, parallelograms and mixed meshes), and
+        otherwise is "fused_volume" for triangles at p <= 3, quadrilaterals
+        (f32 only at p = 3) and f64 tetrahedra at p = 1, else "fused"
+        (tetrahedra at p = 2: "separate")."""
         self.dm.rk_form = self.RK_FORMS[form]
 
     def set_volume_form(self, form: str = "default") -> None:

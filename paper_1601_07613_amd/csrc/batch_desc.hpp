@@ -21,13 +21,15 @@ struct Entry {
     const uint8_t *face_code;
     const double *face_geo;
     const double *elem_geo;
+    const int32_t *slots;  // element -> face slots (element pass; may be null otherwise)
     double *U;   // f64 state
     char *ws;    // SSP-RK3 workspace of this mesh (rk_ws layout)
     double dt;
     int64_t n_face, n_elem, n_dof;
     int64_t color_off[kMaxColors + 1];
     int32_t blk_face[kMaxColors];  // first work-group of this mesh in the launch of each color
-    int32_t blk_elem, blk_dof;     // first work-group in element-wise / DOF-wise launches
+    int32_t blk_elem, blk_dof, blk_stage;  // first work-group in element-wise / DOF-wise / element-pass launches
+    int32_t max_slots;
 };
 
 struct Header {
@@ -37,13 +39,16 @@ struct Header {
     // the stage combination into the last color's launch and (fuse_volume)
     // the volume term into the first color's
     int32_t fuse_combine, fuse_volume;
+    // > 0: the RK step runs the one-pass element stage, with kernels that hold
+    // this many face slots per element
+    int32_t elem_slots;
     int32_t nblk_face[kMaxColors];
-    int32_t nblk_elem, nblk_dof;
+    int32_t nblk_elem, nblk_dof, nblk_stage;
     const double *tables;
     int64_t off_trace, off_proj, off_vb, off_vd;  // into tables, in doubles
     int64_t off_entries;
     int64_t off_map_face[kMaxColors];
-    int64_t off_map_elem, off_map_dof;
+    int64_t off_map_elem, off_map_dof, off_map_stage;
     int64_t total_bytes;
 };
 

@@ -5,6 +5,7 @@
 #include <string>
 #include <type_traits>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -12,6 +13,7 @@
 #include "../batch_desc.hpp"
 #include "../host/internal.hpp"
 #include "batch.hpp"
+#include "element_launch.hpp"
 #include "layout_dev.hpp"
 #include "surface.hpp"
 #include "surface_pair.hpp"
@@ -532,12 +534,20 @@ dgc_status dgc_rk_step(const dgc_dmesh *dm, double *U, double dt, int32_t varian
     const double *x_in[3] = {U, U, U};
     const double *stage_in[3] = {U, U1, U2};
     double *stage_out[3] = {U1, U2, U};
+    if (dm->rk_form < DGC_RK_DEFAULT || dm->rk_form > DGC_RK_FUSED_VOLUME)
+        return fail(DGC_E_ARG, "dgc_dmesh: unknown rk_form");
+    if (variant == DGC_SURF_COLORED && dm->rk_form == DGC_RK_DEFAULT && dm->vol_form == DGC_VOL_DEFAULT &&
+        dgc::element_stage_ok(dm, precision)) {
+        if ((s = check_colors(dm)) != DGC_OK) return s;
+        for (int stg = 0; stg < 3 && s == DGC_OK; ++stg)
+            s = dgc::launch_element_stage(dm, ti, precision, stage_in[stg], stg == 0 ? nullptr : U, stage_out[stg],
+                                          a[stg], b[stg], dt, st);
+        return s;
+    }
     if (shadow) {
         hipLaunchKernelGGL(dgc_dev::to_f32_kernel, dim3(grid_for((int64_t)n)), dim3(kBlock), 0, st, (int64_t)n, U, shadow);
         if ((s = hip_check("f32 shadow launch")) != DGC_OK) return s;
     }
-    if (dm->rk_form < DGC_RK_DEFAULT || dm->rk_form > DGC_RK_FUSED_VOLUME)
-        return fail(DGC_E_ARG, "dgc_dmesh: unknown rk_form");
     // a small mesh: the whole step in one work-group (see DGC_RK_BLOCK)
     const bool block_ok = !shadow && variant == DGC_SURF_COLORED && dm->elem_type != DGC_MIXED;
     if (dm->rk_form == DGC_RK_BLOCK && !block_ok)
@@ -853,7 +863,10 @@ dgc_status dgc_batch_describe(int32_t n_mesh, const dgc_dmesh *meshes, double *c
     for (int32_t i = 0; i < n_mesh; ++i) nc = meshes[i].n_colors > nc ? meshes[i].n_colors : nc;
     // work-group counts
     std::vector<int64_t> nb_face(nc, 0);
-    int64_t nb_elem = 0, nb_dof = 0;
+    int64_t nb_elem = 0, nb_dof = 0, nb_stage = 0;
+    // the element pass, where every member can run it
+    const int epb = dgc::element_stage_elems(ti.dim);
+    int32_t elem_slots = 0;
     for (int32_t i = 0; i < n_mesh; ++i) {
         const dgc_dmesh &d = meshes[i];
         for (int c = 0; c < nc; ++c) {
@@ -862,10 +875,14 @@ dgc_status dgc_batch_describe(int32_t n_mesh, const dgc_dmesh *meshes, double *c
         }
         nb_elem += (d.n_elem * vteam + kBlock - 1) / kBlock;
         nb_dof += (d.n_elem * d.n_var * d.n_p + kBlock - 1) / kBlock;
+        nb_stage += (d.n_elem + epb - 1) / epb;
+        elem_slots = dgc::element_stage_ok(&d, precision) ? std::max(elem_slots, d.max_slots) : INT32_MAX;
     }
+    if (elem_slots == INT32_MAX) elem_slots = nb_stage = 0;
     for (int c = 0; c < nc; ++c)
         if (nb_face[c] > INT32_MAX) return fail(DGC_E_ARG, "dgc_batch_describe: batch too large");
-    if (nb_elem > INT32_MAX || nb_dof > INT32_MAX) return fail(DGC_E_ARG, "dgc_batch_describe: batch too large");
+    if (nb_elem > INT32_MAX || nb_dof > INT32_MAX || nb_stage > INT32_MAX)
+        return fail(DGC_E_ARG, "dgc_batch_describe: batch too large");
     dgc_batch::Header h{};
     h.magic = dgc_batch::kMagic;
     h.n_mesh = n_mesh;
@@ -911,6 +928,10 @@ dgc_status dgc_batch_describe(int32_t n_mesh, const dgc_dmesh *meshes, double *c
     h.off_map_dof = off;
     h.nblk_dof = (int32_t)nb_dof;
     off += 4 * nb_dof;
+    h.elem_slots = elem_slots;
+    h.off_map_stage = off;
+    h.nblk_stage = (int32_t)nb_stage;
+    off += 4 * nb_stage;
     h.total_bytes = off;
     if (needed) *needed = (size_t)off;
     if (!host_desc) return DGC_OK;
@@ -920,7 +941,7 @@ dgc_status dgc_batch_describe(int32_t n_mesh, const dgc_dmesh *meshes, double *c
     std::memcpy(out, &h, sizeof(h));
     dgc_batch::Entry *ent = reinterpret_cast<dgc_batch::Entry *>(out + h.off_entries);
     std::vector<int64_t> cur(nc, 0);
-    int64_t ce = 0, cd = 0;
+    int64_t ce = 0, cd = 0, cs = 0;
     for (int32_t i = 0; i < n_mesh; ++i) {
         const dgc_dmesh &d = meshes[i];
         dgc_batch::Entry &e = ent[i];
@@ -928,6 +949,8 @@ dgc_status dgc_batch_describe(int32_t n_mesh, const dgc_dmesh *meshes, double *c
         e.face_code = d.face_code;
         e.face_geo = d.face_geo;
         e.elem_geo = d.elem_geo;
+        e.slots = d.elem_slots;
+        e.max_slots = d.max_slots;
         e.U = U[i];
         e.ws = static_cast<char *>(ws[i]);
         e.dt = dt[i];
@@ -952,6 +975,13 @@ dgc_status dgc_batch_describe(int32_t n_mesh, const dgc_dmesh *meshes, double *c
         for (int64_t b = 0; b < nd; ++b) md[cd + b] = i;
         ce += ne;
         cd += nd;
+        if (elem_slots) {
+            e.blk_stage = (int32_t)cs;
+            int32_t *mst = reinterpret_cast<int32_t *>(out + h.off_map_stage);
+            const int64_t ns = (d.n_elem + epb - 1) / epb;
+            for (int64_t b = 0; b < ns; ++b) mst[cs + b] = i;
+            cs += ns;
+        }
     }
     return DGC_OK;
 }
@@ -986,6 +1016,12 @@ dgc_status dgc_rk_step_batched(const void *host_desc, const void *dev_desc, void
     if (!dev_desc) return fail(DGC_E_ARG, "dgc_rk_step_batched: null device descriptor");
     hipStream_t st = static_cast<hipStream_t>(stream);
     const char *dev = static_cast<const char *>(dev_desc);
+    if (h.elem_slots > 0) {
+        dgc_status s = DGC_OK;
+        for (int stage = 0; stage < 3 && s == DGC_OK; ++stage)
+            s = dgc::launch_element_stage_batched(h, dev, stage, st);
+        return s;
+    }
     const bool f32 = h.precision == DGC_F32;
     if (f32) {
         hipLaunchKernelGGL(dgc_dev::batch_to_f32_kernel, dim3(h.nblk_dof), dim3(kBlock), 0, st, dev);

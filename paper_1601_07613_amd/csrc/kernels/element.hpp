@@ -1,0 +1,545 @@
+// One SSP-RK3 stage in one pass over the elements.
+//
+// Every element evaluates its volume term, the fluxes of all its faces (a
+// face between two elements is evaluated by both, each keeping its own side)
+// and the stage combination  out = a x + b (y + dt rhs)  with y the stage
+// input; the right-hand side never leaves the registers.  Each element writes
+// only its own record, so no two work-items touch the same memory and one
+// launch covers the whole mesh: a stage reads y (once as the element's own
+// record and again, mostly from cache, as its neighbours'), x, the geometry,
+// and writes out, where the colored launches read and write the right-hand
+// side once per color besides.
+//
+// A wave owns EW elements, M lanes each (lane = conserved variable m of
+// element e; EW = 16 for M = 4, 12 for M = 5).  For a group of FG face slots:
+//   1. lane (e, m) forms variable m's traces of both sides at the Q points of
+//      every face and stores them in the wave's LDS region;
+//   2. the wave's lanes share out the EW * FG * Q points: one lane evaluates
+//      the Rusanov flux of all variables at its point, once, and overwrites
+//      the neighbour's trace with w_q |f| F*;
+//   3. lane (e, m) projects its variable's fluxes onto its N_p modes.
+// The exchange stays inside a wave, whose LDS operations execute in order, so
+// no work-group barrier is needed and the waves of a work-group run on
+// independently.  The volume term is evaluated by the team of four lanes with
+// register exchanges (M = 4) or through the same LDS region (M = 5).
+// Contributions are added in slot order, the color order of the layout (in
+// f64 on conforming meshes in the order of the element's local faces).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <utility>
+
+#include "batch_dev.hpp"
+#include "euler_dev.hpp"
+#include "volume_team.hpp"
+
+namespace dgc_dev {
+
+// one mesh's arrays and one stage's combination
+struct ElemStageArgs {
+    const int32_t *slots;      // [ms][n_elem] 2 * face + side, -1 padded
+    const int32_t *face_lr;    // [2][n_face]
+    const uint8_t *face_code;  // [2][n_face]
+    const double *face_geo;    // [DIM + 3][n_face]
+    const double *elem_geo;    // [DIM * DIM + 1][n_elem]
+    const int8_t *kind;        // [n_elem], mixed meshes
+    int64_t n_elem, n_face;
+    const double *y, *x;       // stage input; stage-0 state (null: y itself)
+    double *out;
+    float *shadow;             // f32 form: the new state rounded to f32 (may be null)
+    double a, b, dt;
+};
+
+// the basis tables of the element type
+struct ElemTables {
+    const double *trace, *proj, *vb, *vd;
+    int n_codes;
+};
+
+// 1/x with a second Newton step: within a rounding of the quotient (the
+// factor multiplies every trace and projection of the element)
+__device__ __forceinline__ double exact_recip(double x) {
+    const double r = dev_recip<double>(x);
+    return __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
+}
+
+// x as it is rounded here: not fused into the operation that uses it
+template <class T>
+__device__ __forceinline__ T rounded(T x) {
+    asm("" : "+v"(x));
+    return x;
+}
+
+// order the wave's LDS writes before its later LDS reads (compiler only: the
+// hardware executes one wave's LDS operations in order)
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Launch shape and LDS sizes, shared by host and device.
+template <int DIM, int NP, int Q, int QV, int FS, bool MIXED, class T>
+struct ElemCfg {
+    static constexpr int M = DIM + 2;
+    static constexpr int EW = 64 / M;            // elements per wave
+    static constexpr int WAVES = 4;
+    static constexpr int BLOCK = 64 * WAVES;
+    static constexpr int EPB = EW * WAVES;       // elements per work-group
+    static constexpr int NG = DIM + 2;           // side geometry: normal, |f|, 1/sqrt(det J) of the neighbour
+    static constexpr int NF = DIM == 3 || FS == 4 ? 4 : 3;  // faces of a conforming element
+    static constexpr int NO = DIM == 2 ? 4 : 6;  // orientation codes per local face
+    // f32: own and neighbour's tables by face code, in slot order, rounded as
+    // the colored kernels round; f64 on conforming meshes whose face rule
+    // looks the same from both sides: the sides in the order of the element's
+    // local faces, so that its own tables are the same for every lane and
+    // come through the scalar cache (FACES)
+    static constexpr bool PROJ = sizeof(T) == 4;
+    static constexpr bool FACES = !PROJ && !MIXED && FS == NF && (DIM == 2 || Q == 3);
+    // The wave's region: planes of one variable's traces at the group's
+    // points, own then neighbour's, then planes of the side geometry.  Odd
+    // plane lengths spread a store of the M variables over the banks.
+    static constexpr int plane(int fg) { return (EW * fg * Q) | 1; }
+    static constexpr int gplane(int fg) { return (EW * fg) | 1; }
+    static constexpr int group_len(int fg) { return 2 * M * plane(fg) + NG * gplane(fg); }
+    // face slots per group: what keeps the wave's region within 11 KB (three
+    // waves per SIMD); all four sides at N_p = 9 (15 KB: the registers leave
+    // two waves anyway; 589,824 parallelograms 234 us a stage, with three
+    // sides and one 260); one at N_p >= 16 (two sides' modes do not fit the
+    // registers: 39,762 triangles at p = 5 94 us, with two 162)
+    static constexpr int BUDGET = (NP >= 16 ? 7 : (NP == 9 && !PROJ && !MIXED ? 15 : 11)) * 1024;
+    static constexpr int fit(int fg) { return fg <= 1 || group_len(fg) * (int)sizeof(T) <= BUDGET ? fg : fit(fg - 1); }
+    static constexpr int FG = fit(FS);
+    // the volume term by register exchanges of the team of four lanes, or
+    // (M = 5) through the region, QC points at a time; through the region for
+    // M = 4 too took 236 instead of 231 us on 991,232 triangles at p = 2
+    static constexpr bool VTEAM = M == 4;
+    static constexpr int vplane(int qc) { return (EW * qc) | 1; }
+    static constexpr int vfit(int qc) { return qc <= 1 || M * DIM * vplane(qc) <= group_len(FG) ? qc : vfit(qc - 1); }
+    static constexpr int QC = vfit(QV);
+    static constexpr int REGION = group_len(FG) > M * DIM * vplane(QC) ? group_len(FG) : M * DIM * vplane(QC);
+    __host__ __device__ static constexpr int tab_len(int n_codes) {
+        return PROJ ? 2 * n_codes * Q * NP : n_codes * Q * NP + Q;
+    }
+    static constexpr bool VFUSED = PROJ && M == 4 && !MIXED && FS <= 4;
+    static constexpr int VTAB = MIXED ? 2 * (1 + DIM) * QV * NP : 0;  // mixed meshes: both kinds' volume tables
+
+    __host__ __device__ static constexpr size_t lds_bytes(int n_codes) {
+        return (size_t)(tab_len(n_codes) + VTAB + WAVES * REGION) * sizeof(T);
+    }
+};
+
+// Volume term of M = 5 variables through the wave's LDS region: the point
+// values are exchanged, each point's flux is evaluated once.
+template <int DIM, int NP, int QV, int QC, int EW, class T>
+__device__ __forceinline__ void volume_wave(int lane, int e, int m, bool lane_ok, const T (&Ji)[DIM * DIM], T isq,
+                                            const double *__restrict__ vb, const double *__restrict__ vd,
+                                            const T (&c)[NP], T *region, T (&acc)[NP]) {
+    constexpr int M = DIM + 2;
+    constexpr int P = (EW * QC) | 1;
+#pragma unroll 1
+    for (int q0 = 0; q0 < QV; q0 += QC) {
+        const int nq = QV - q0 < QC ? QV - q0 : QC;
+        if (lane_ok) {
+#pragma unroll 2
+            for (int q = 0; q < nq; ++q) {
+                T t = 0;
+#pragma unroll
+                for (int j = 0; j < NP; ++j) t += T(vb[(q0 + q) * NP + j]) * c[j];
+                region[m * P + e * QC + q] = t * isq;
+            }
+        }
+        wave_lds_fence();
+        for (int t = lane; t < EW * QC; t += 64) {
+            T u[M], F[M * DIM];
+#pragma unroll
+            for (int i = 0; i < M; ++i) u[i] = region[i * P + t];
+            phys_flux<DIM, T>(u, F);
+#pragma unroll
+            for (int i = 0; i < M * DIM; ++i) region[i * P + t] = F[i];
+        }
+        wave_lds_fence();
+        if (lane_ok) {
+#pragma unroll 1
+            for (int q = 0; q < nq; ++q) {
+                const T *v = region + m * DIM * P + e * QC + q;
+                T F[DIM];
+#pragma unroll
+                for (int d = 0; d < DIM; ++d) F[d] = v[d * P];
+#pragma unroll
+                for (int d = 0; d < DIM; ++d) {
+                    T g = 0;
+#pragma unroll
+                    for (int i = 0; i < DIM; ++i) g += Ji[d * DIM + i] * F[i];
+#pragma unroll
+                    for (int j = 0; j < NP; ++j) acc[j] = dev_fma(T(vd[(d * QV + q0 + q) * NP + j]), g, acc[j]);
+                }
+            }
+        }
+        wave_lds_fence();
+    }
+}
+
+// Where point q of a face, in the order of the element's own local face,
+// stands among the face's points seen through orientation o: 2D reversed for
+// odd o; 3D (three points, one per vertex) the inverse of the o-th
+// permutation in lexicographic order, two bits an entry.
+template <int DIM, int Q>
+__device__ __forceinline__ int point_place(int o, int q) {
+    if constexpr (DIM == 2) {
+        return (o & 1) ? Q - 1 - q : q;
+    } else {
+        // inverses of 012 021 102 120 201 210
+        constexpr uint64_t inv = 0x24ull | 0x18ull << 6 | 0x21ull << 12 | 0x12ull << 18 | 0x09ull << 24 | 0x06ull << 30;
+        return (int)(inv >> (6 * o + 2 * q)) & 3;
+    }
+}
+
+// The stage of the EPB elements from k0 on (every thread of the work-group
+// calls; s_tab holds the trace tables, the face weights or projection tables,
+// then on mixed meshes the volume tables).
+template <int DIM, int NP, int Q, int QV, int FS, bool MIXED, class T>
+__device__ __forceinline__ void element_stage(const ElemStageArgs &A, const ElemTables &tab, int64_t k0, int ms,
+                                              const T *s_tab, T *s_regions) {
+    using C = ElemCfg<DIM, NP, Q, QV, FS, MIXED, T>;
+    constexpr int M = C::M, EW = C::EW, FG = C::FG;
+    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+    const int e = lane / M, m = lane - e * M;
+    const int64_t k = k0 + wave * EW + e;
+    const bool lane_ok = e < EW && k < A.n_elem;
+    const int64_t K = A.n_elem, E = A.n_face;
+    const int64_t kc = lane_ok ? k : 0;  // every read is of a valid element
+    const int nc = tab.n_codes;
+    const T *s_tr = s_tab, *s_w = s_tab + nc * Q * NP;  // weights (f64) or projection tables (f32)
+    T *region = s_regions + wave * C::REGION;
+
+    int32_t slot[FS];
+#pragma unroll
+    for (int s = 0; s < FS; ++s) slot[s] = s < ms ? A.slots[(int64_t)s * K + kc] : -1;
+    double yv[NP];
+    const size_t base = ((size_t)kc * M + m) * NP;
+#pragma unroll
+    for (int j = 0; j < NP; ++j) yv[j] = A.y[base + j];
+    T Ji[DIM * DIM];
+    double sq;
+    load_elem_geo<DIM, T>(kc, K, A.elem_geo, Ji, sq);
+    const int kind = MIXED ? (A.kind[kc] ? 1 : 0) : 0;
+
+    // the sides: neighbour (-1 where there is none), codes; conditions joined
+    // without branches, so that the reads of all sides are in flight together
+    int32_t nb[FS];
+    int co[FS], cn[FS];
+    bool ok[FS];
+    const uint32_t E2 = (uint32_t)(2 * E);
+#pragma unroll
+    for (int i = 0; i < FS; ++i) {
+        const uint32_t sl = (uint32_t)slot[i];
+        const bool in = sl < E2;
+        const uint32_t f = in ? sl >> 1 : 0u;
+        const bool right = sl & 1;
+        nb[i] = A.face_lr[(right ? 0 : E) + f];
+        co[i] = A.face_code[(right ? E : 0) + f];
+        cn[i] = A.face_code[(right ? 0 : E) + f];
+        // a malformed face (ids or codes out of range) is skipped, never dereferenced
+        ok[i] = lane_ok & in & (nb[i] < K) & (co[i] < nc) & (cn[i] < nc) & ((nb[i] >= 0) | !right);
+        nb[i] = ok[i] ? nb[i] : -1;
+        co[i] = ok[i] ? co[i] : 0;
+        cn[i] = ok[i] ? cn[i] : 0;
+    }
+    // in the order of the local faces
+    if constexpr (C::FACES) {
+        int32_t sl2[FS], nb2[FS];
+        int co2[FS], cn2[FS];
+        bool ok2[FS];
+#pragma unroll
+        for (int f = 0; f < FS; ++f) {
+            sl2[f] = -1;
+            nb2[f] = -1;
+            co2[f] = cn2[f] = 0;
+            ok2[f] = false;
+#pragma unroll
+            for (int i = 0; i < FS; ++i) {
+                const bool hit = ok[i] & ((uint32_t)(co[i] - f * C::NO) < (uint32_t)C::NO);
+                sl2[f] = hit ? slot[i] : sl2[f];
+                nb2[f] = hit ? nb[i] : nb2[f];
+                co2[f] = hit ? co[i] - f * C::NO : co2[f];  // the orientation
+                cn2[f] = hit ? cn[i] : cn2[f];
+                ok2[f] = ok2[f] | hit;
+            }
+        }
+#pragma unroll
+        for (int f = 0; f < FS; ++f) {
+            slot[f] = sl2[f];
+            nb[f] = nb2[f];
+            co[f] = co2[f];
+            cn[f] = cn2[f];
+            ok[f] = ok2[f];
+        }
+    }
+
+    T c[NP], acc[NP];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+        c[j] = T(yv[j]);
+        acc[j] = T(0);
+    }
+    const double isq_d = sizeof(T) == 8 ? exact_recip(sq) : 1.0 / sq;
+    const T isq = T(isq_d);
+
+    // the stage-0 state of the combination, read up front: it arrives while
+    // the stage is computed (N_p >= 15: at the end, the registers run out)
+    constexpr bool LATE_X = NP >= 15;
+    double xv[NP];
+    auto read_x = [&]() {
+        if (A.x) {
+#pragma unroll
+            for (int j = 0; j < NP; ++j) xv[j] = A.x[base + j];
+        } else {
+#pragma unroll
+            for (int j = 0; j < NP; ++j) xv[j] = yv[j];
+        }
+    };
+    if constexpr (!LATE_X) read_x();
+
+    // volume term, without its factor sqrt(det J) where the first slot applies
+    // it (the first group's neighbour reads are in flight by then)
+    const double vsq = C::VFUSED ? 1.0 : sq;
+    auto volume = [&]() {
+        if constexpr (C::VTEAM) {
+            if constexpr (MIXED) {
+                const T *s_vb = s_tab + C::tab_len(nc);
+                const T *s_vd = s_vb + 2 * QV * NP;
+                volume_team_core_geo<DIM, NP, QV, T, T>(m, Ji, vsq, isq_d, s_vb + kind * QV * NP,
+                                                        s_vd + kind * DIM * QV * NP, c, acc);
+            } else {
+                volume_team_core_geo<DIM, NP, QV, T, double>(m, Ji, vsq, isq_d, tab.vb, tab.vd, c, acc);
+            }
+        } else {
+            volume_wave<DIM, NP, QV, C::QC, EW, T>(lane, e, m, lane_ok, Ji, isq, tab.vb, tab.vd, c, region, acc);
+#pragma unroll
+            for (int j = 0; j < NP; ++j) acc[j] *= T(vsq);
+        }
+    };
+
+    // one group of face slots
+    auto group = [&](auto first) {
+        constexpr int s0 = decltype(first)::value;
+        constexpr int G = FS - s0 < FG ? FS - s0 : FG;
+        constexpr int P = C::plane(G), GP = C::gplane(G);
+        T *s_own = region, *s_nb = region + M * P, *s_geo = region + 2 * M * P;
+        // lane m of an element reads the geometry of its group's sides m, m + M
+        constexpr int GS = (G + M - 1) / M;
+        double gv[GS][C::NG];
+        bool gok[GS], gright[GS], gwall[GS];
+#pragma unroll
+        for (int g = 0; g < GS; ++g) {
+            uint32_t sl = 0;
+            gok[g] = gwall[g] = false;
+#pragma unroll
+            for (int i = 0; i < G; ++i) {
+                    const bool mine = i == g * M + m;
+                sl = mine & ok[s0 + i] ? (uint32_t)slot[s0 + i] : sl;
+                gok[g] = gok[g] | (mine & ok[s0 + i]);
+                gwall[g] = gwall[g] | (mine & (nb[s0 + i] < 0));
+            }
+            gright[g] = sl & 1;
+            const double *fg = A.face_geo + (sl >> 1);
+#pragma unroll
+            for (int d = 0; d <= DIM; ++d) gv[g][d] = fg[d * E];
+            gv[g][DIM + 1] = fg[(DIM + (gright[g] ? 1 : 2)) * E];
+        }
+        T cnb[G][NP];
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const int64_t b = nb[s0 + i] >= 0 ? nb[s0 + i] : kc;
+            const double *u = A.y + ((size_t)b * M + m) * NP;
+#pragma unroll
+            for (int j = 0; j < NP; ++j) cnb[i][j] = T(u[j]);
+        }
+        if (s0 == 0) volume();
+#pragma unroll
+        for (int g = 0; g < GS; ++g) {
+            if (!gok[g]) continue;
+            T *q = s_geo + e * G + g * M + m;
+#pragma unroll
+            for (int d = 0; d < DIM; ++d) q[d * GP] = T(gv[g][d]);
+            q[DIM * GP] = T(C::PROJ ? gv[g][DIM] * isq_d : gv[g][DIM]);
+            // negative: this element is the face's right one; 0: wall
+            const T is = gwall[g] ? T(0) : T(gv[g][DIM + 1]);
+            q[(DIM + 1) * GP] = gright[g] ? -is : is;
+        }
+        wave_lds_fence();
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const int s = s0 + i;
+            if (!ok[s]) continue;
+            T *po = s_own + m * P + (e * G + i) * Q, *pn = s_nb + m * P + (e * G + i) * Q;
+            const T sn = s_geo[(DIM + 1) * GP + e * G + i], isn = sn < T(0) ? -sn : sn;
+            const T *tn = s_tr + cn[s] * Q * NP, *to = s_tr + co[s] * Q * NP;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                T t = 0, u = 0;
+#pragma unroll
+                for (int j = 0; j < NP; ++j) {
+                    t += (C::FACES ? T(tab.trace[(s * C::NO * Q + q) * NP + j]) : to[q * NP + j]) * c[j];
+                    u += tn[q * NP + j] * cnb[i][j];
+                }
+                po[C::FACES ? point_place<DIM, Q>(co[s], q) : q] = t * isq;
+                pn[q] = u * isn;
+            }
+        }
+        wave_lds_fence();
+        for (int t = lane; t < EW * G * Q; t += 64) {
+            const int side = t / Q;
+            const T *g = s_geo + side;
+            T n[DIM], uL[M], uR[M];
+#pragma unroll
+            for (int d = 0; d < DIM; ++d) n[d] = g[d * GP];
+            const T isn = g[(DIM + 1) * GP];
+            // the flux in the face's own left-to-right sense, which both of
+            // its elements evaluate alike
+            const T *pl = (isn < T(0) ? s_nb : s_own) + t, *pr = (isn < T(0) ? s_own : s_nb) + t;
+#pragma unroll
+            for (int i = 0; i < M; ++i) {
+                uL[i] = pl[i * P];
+                uR[i] = pr[i * P];
+            }
+            if (isn == T(0)) wall_ghost<DIM, T>(uL, n, uR);
+            T F[M], w = T(1);
+            if constexpr (C::PROJ) {
+                rusanov_components<DIM, T>(uL, uR, n, F);
+            } else {
+                rusanov<DIM, T>(uL, uR, n, F);
+                w = g[DIM * GP] * s_w[t - side * Q];
+                w = isn < T(0) ? w : -w;
+            }
+#pragma unroll
+            for (int i = 0; i < M; ++i) s_nb[i * P + t] = C::PROJ ? F[i] : F[i] * w;
+        }
+        wave_lds_fence();
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const int s = s0 + i;
+            if (!ok[s]) {
+                if (C::VFUSED && s == 0) {
+#pragma unroll
+                    for (int j = 0; j < NP; ++j) acc[j] *= T(sq);
+                }
+                continue;
+            }
+            const T *pr = (C::PROJ ? s_w : s_tr) + co[s] * Q * NP;
+            const T *pf = s_nb + m * P + (e * G + i) * Q;
+            T f[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                f[q] = pf[C::FACES ? point_place<DIM, Q>(co[s], q) : q];
+                if (!C::PROJ) f[q] *= isq;  // the sign is in the flux
+            }
+            if constexpr (C::PROJ) {
+                const T scale = s_geo[DIM * GP + e * G + i];
+                const bool right = slot[s] & 1;
+#pragma unroll
+                for (int j = 0; j < NP; ++j) {
+                    T a = 0;
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) a += pr[q * NP + j] * f[q];
+                    // the first slot also scales the volume sum, rounded as
+                    // the colored kernel that carries the volume term rounds
+                    if (C::VFUSED && s == 0)
+                        acc[j] = right ? dev_fma(a, scale, rounded(acc[j] * T(sq)))
+                                       : dev_fma(acc[j], T(sq), -rounded(scale * a));
+                    else acc[j] = dev_fma(a, right ? scale : -scale, acc[j]);
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < Q; ++q)
+#pragma unroll
+                    for (int j = 0; j < NP; ++j)
+                        acc[j] = dev_fma(C::FACES ? T(tab.trace[(s * C::NO * Q + q) * NP + j]) : pr[q * NP + j], f[q],
+                                         acc[j]);
+            }
+        }
+        if constexpr (s0 + FG < FS) wave_lds_fence();
+    };
+    [&]<int... I>(std::integer_sequence<int, I...>) {
+        (group(std::integral_constant<int, I * FG>{}), ...);
+    }(std::make_integer_sequence<int, (FS + FG - 1) / FG>{});
+    if (!lane_ok) return;
+    if constexpr (LATE_X) read_x();
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+        const double v = A.a * xv[j] + A.b * (yv[j] + A.dt * (double)acc[j]);
+        A.out[base + j] = v;
+        if (sizeof(T) == 4 && A.shadow) A.shadow[base + j] = (float)v;
+    }
+}
+
+// the basis tables into LDS (every thread; ends with a work-group barrier)
+template <int DIM, int NP, int Q, int QV, int FS, bool MIXED, class T>
+__device__ __forceinline__ void stage_elem_tables(T *s, const ElemTables &tab) {
+    const int n = tab.n_codes * Q * NP;
+    using C = ElemCfg<DIM, NP, Q, QV, FS, MIXED, T>;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        s[i] = T(tab.trace[i]);
+        if constexpr (C::PROJ) s[n + i] = T(tab.proj[i]);
+    }
+    // the projection table is the weights times the trace table: the weights
+    // from its constant mode, whose trace is the same positive value everywhere
+    if constexpr (!C::PROJ)
+        for (int q = threadIdx.x; q < Q; q += blockDim.x) s[n + q] = T(tab.proj[q * NP] / tab.trace[q * NP]);
+    if constexpr (MIXED) {
+        T *v = s + C::tab_len(tab.n_codes);
+        for (int i = threadIdx.x; i < 2 * QV * NP; i += blockDim.x) v[i] = T(tab.vb[i]);
+        for (int i = threadIdx.x; i < 2 * DIM * QV * NP; i += blockDim.x) v[2 * QV * NP + i] = T(tab.vd[i]);
+    }
+    __syncthreads();
+}
+
+template <int DIM, int NP, int Q, int QV, int FS, bool MIXED, class T>
+__global__ __launch_bounds__((ElemCfg<DIM, NP, Q, QV, FS, MIXED, T>::BLOCK)) void element_stage_kernel(ElemStageArgs A, ElemTables tab, int ms) {
+    using C = ElemCfg<DIM, NP, Q, QV, FS, MIXED, T>;
+    extern __shared__ unsigned char smem_raw[];
+    T *s_tab = reinterpret_cast<T *>(smem_raw);
+    stage_elem_tables<DIM, NP, Q, QV, FS, MIXED, T>(s_tab, tab);
+    element_stage<DIM, NP, Q, QV, FS, MIXED, T>(A, tab, (int64_t)blockIdx.x * C::EPB, ms, s_tab,
+                                                s_tab + C::tab_len(tab.n_codes) + C::VTAB);
+}
+
+// The stage of every mesh of a batch: a work-group finds its mesh in the
+// descriptor's block map.
+template <int DIM, int NP, int Q, int QV, int FS, bool MIXED, class T>
+__global__ __launch_bounds__((ElemCfg<DIM, NP, Q, QV, FS, MIXED, T>::BLOCK)) void batch_element_stage_kernel(const char *__restrict__ desc, int stage) {
+    using C = ElemCfg<DIM, NP, Q, QV, FS, MIXED, T>;
+    extern __shared__ unsigned char smem_raw[];
+    T *s_tab = reinterpret_cast<T *>(smem_raw);
+    const Header *h = bh(desc);
+    const double *tables = gptr(h->tables);
+    const ElemTables tab{tables + h->off_trace, tables + h->off_proj, tables + h->off_vb, tables + h->off_vd,
+                         h->n_codes};
+    stage_elem_tables<DIM, NP, Q, QV, FS, MIXED, T>(s_tab, tab);
+    const int32_t i = reinterpret_cast<const int32_t *>(desc + h->off_map_stage)[blockIdx.x];
+    const Entry *en = bentry(desc, i);
+    const Member mb = member(en, sizeof(T) == 4);
+    ElemStageArgs A;
+    A.slots = gptr(en->slots);
+    A.face_lr = mb.face_lr;
+    A.face_code = mb.face_code;
+    A.face_geo = mb.face_geo;
+    A.elem_geo = mb.elem_geo;
+    A.kind = nullptr;
+    A.n_elem = en->n_elem;
+    A.n_face = en->n_face;
+    A.y = stage == 0 ? mb.U : (stage == 1 ? mb.w.U1 : mb.w.U2);
+    A.x = stage == 0 ? nullptr : mb.U;
+    A.out = stage == 0 ? mb.w.U1 : (stage == 1 ? mb.w.U2 : mb.U);
+    // the f32 shadow that the batched volume and surface calls read is left
+    // as a step with separate combinations leaves it: the last stage's input
+    A.shadow = stage == 1 ? mb.w.shadow : nullptr;
+    A.a = stage == 0 ? 0.0 : (stage == 1 ? 0.75 : 1.0 / 3.0);
+    A.b = stage == 0 ? 1.0 : (stage == 1 ? 0.25 : 2.0 / 3.0);
+    A.dt = en->dt;
+    element_stage<DIM, NP, Q, QV, FS, MIXED, T>(A, tab, ((int64_t)blockIdx.x - en->blk_stage) * C::EPB, en->max_slots,
+                                                s_tab, s_tab + C::tab_len(tab.n_codes) + C::VTAB);
+}
+
+}  // namespace dgc_dev

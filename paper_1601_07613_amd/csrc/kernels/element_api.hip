@@ -1,0 +1,135 @@
+// Launches of the one-pass element stage.
+#include <hip/hip_runtime.h>
+
+#include <string>
+
+#include "element.hpp"
+#include "element_launch.hpp"
+
+namespace dgc {
+
+namespace {
+
+// run f with the kernels' shape for an element type, order and number of face
+// slots (f's argument names the template parameters)
+template <int DIM, int NP, int Q, int QV, int FS, bool MIXED>
+struct Shape {
+    static constexpr int kDim = DIM, kNp = NP, kQ = Q, kQv = QV, kFs = FS;
+    static constexpr bool kMixed = MIXED;
+};
+template <class F>
+dgc_status dispatch(int elem_type, int p, int max_slots, F &&f) {
+#define DGC_ELEM(P, DIM, NP, Q, QV, FS, MIXED) \
+    case P: return f(Shape<DIM, NP, Q, QV, FS, MIXED>{});
+    if (elem_type == DGC_TRI && max_slots <= 3) {
+        switch (p) {
+            DGC_ELEM(0, 2, 1, 1, 1, 3, false)
+            DGC_ELEM(1, 2, 3, 2, 4, 3, false)
+            DGC_ELEM(2, 2, 6, 3, 9, 3, false)
+            DGC_ELEM(3, 2, 10, 4, 16, 3, false)
+            DGC_ELEM(4, 2, 15, 5, 25, 3, false)
+            DGC_ELEM(5, 2, 21, 6, 36, 3, false)
+        }
+    } else if (elem_type == DGC_TRI) {
+        switch (p) {
+            DGC_ELEM(0, 2, 1, 1, 1, 6, false)
+            DGC_ELEM(1, 2, 3, 2, 4, 6, false)
+            DGC_ELEM(2, 2, 6, 3, 9, 6, false)
+            DGC_ELEM(3, 2, 10, 4, 16, 6, false)
+            DGC_ELEM(4, 2, 15, 5, 25, 6, false)
+            DGC_ELEM(5, 2, 21, 6, 36, 6, false)
+        }
+    } else if (elem_type == DGC_QUAD) {
+        switch (p) {
+            DGC_ELEM(0, 2, 1, 1, 1, 4, false)
+            DGC_ELEM(1, 2, 4, 2, 4, 4, false)
+            DGC_ELEM(2, 2, 9, 3, 9, 4, false)
+            DGC_ELEM(3, 2, 16, 4, 16, 4, false)
+        }
+    } else if (elem_type == DGC_MIXED) {
+        switch (p) {
+            DGC_ELEM(0, 2, 1, 1, 1, 4, true)
+            DGC_ELEM(1, 2, 4, 2, 4, 4, true)
+            DGC_ELEM(2, 2, 9, 3, 9, 4, true)
+            DGC_ELEM(3, 2, 16, 4, 16, 4, true)
+        }
+    } else if (elem_type == DGC_TET) {
+        switch (p) {
+            DGC_ELEM(0, 3, 1, 3, 1, 4, false)
+            DGC_ELEM(1, 3, 4, 3, 8, 4, false)
+            DGC_ELEM(2, 3, 10, 9, 27, 4, false)
+        }
+    }
+#undef DGC_ELEM
+    return fail(DGC_E_UNSUPPORTED, "no element stage built for this element type and order");
+}
+
+dgc_status launched(const char *what) {
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(DGC_E_HIP, std::string(what) + ": " + hipGetErrorString(e));
+    return DGC_OK;
+}
+
+template <class S, class T>
+using Cfg = dgc_dev::ElemCfg<S::kDim, S::kNp, S::kQ, S::kQv, S::kFs, S::kMixed, T>;
+
+template <class T>
+dgc_status launch(const dgc_dmesh *dm, const dgc_dev::ElemStageArgs &A, const dgc_dev::ElemTables &tab,
+                  hipStream_t st) {
+    return dispatch(dm->elem_type, dm->p, dm->max_slots, [&](auto shape) {
+        using S = decltype(shape);
+        using C = Cfg<S, T>;
+        hipLaunchKernelGGL((dgc_dev::element_stage_kernel<S::kDim, S::kNp, S::kQ, S::kQv, S::kFs, S::kMixed, T>),
+                           dim3((unsigned)((A.n_elem + C::EPB - 1) / C::EPB)), dim3(C::BLOCK),
+                           C::lds_bytes(tab.n_codes), st, A, tab, dm->max_slots);
+        return launched("element stage launch");
+    });
+}
+
+template <class T>
+dgc_status launch_batch(const dgc_batch::Header &h, const char *dev, int stage, hipStream_t st) {
+    return dispatch(h.elem_type, h.p, h.elem_slots, [&](auto shape) {
+        using S = decltype(shape);
+        if constexpr (S::kMixed) {
+            return fail(DGC_E_UNSUPPORTED, "mixed meshes are not batched");
+        } else {
+            using C = Cfg<S, T>;
+            hipLaunchKernelGGL((dgc_dev::batch_element_stage_kernel<S::kDim, S::kNp, S::kQ, S::kQv, S::kFs, false, T>),
+                               dim3(h.nblk_stage), dim3(C::BLOCK), C::lds_bytes(h.n_codes), st, dev, stage);
+            return launched("batched element stage launch");
+        }
+    });
+}
+
+}  // namespace
+
+bool element_stage_ok(const dgc_dmesh *dm, int32_t precision) {
+    const int most = dm->elem_type == DGC_TRI ? 6 : 4;
+    if (!dm->elem_slots || dm->max_slots <= 0 || dm->max_slots > most) return false;
+    if (precision == DGC_F64) return true;
+    // the f32 form keeps the rounding of the colored kernels, which the
+    // element pass reproduces where those evaluate the volume term by teams
+    if (dm->elem_type == DGC_MIXED) return true;
+    if (dm->elem_type == DGC_TET || dm->n_colors != dm->max_slots) return false;
+    return dm->elem_type == DGC_QUAD || (dm->p <= 3 && dm->max_slots == 3);
+}
+
+dgc_status launch_element_stage(const dgc_dmesh *dm, const dgc_table_info &ti, int32_t precision, const double *y,
+                                const double *x, double *out, double a, double b, double dt, hipStream_t st) {
+    const dgc_dev::ElemStageArgs A{dm->elem_slots, dm->face_lr, dm->face_code, dm->face_geo, dm->elem_geo,
+                                   dm->elem_kind,  dm->n_elem,  dm->n_face,    y,            x,
+                                   out,            nullptr,     a,             b,            dt};
+    const dgc_dev::ElemTables tab{dm->tables + ti.off_trace, dm->tables + ti.off_proj, dm->tables + ti.off_vb,
+                                  dm->tables + ti.off_vd, ti.n_codes};
+    return precision == DGC_F32 ? launch<float>(dm, A, tab, st) : launch<double>(dm, A, tab, st);
+}
+
+int element_stage_elems(int dim) {
+    return dim == 2 ? dgc_dev::ElemCfg<2, 6, 3, 9, 3, false, double>::EPB : dgc_dev::ElemCfg<3, 4, 3, 8, 4, false, double>::EPB;
+}
+
+dgc_status launch_element_stage_batched(const dgc_batch::Header &h, const char *dev, int stage, hipStream_t st) {
+    return h.precision == DGC_F32 ? launch_batch<float>(h, dev, stage, st) : launch_batch<double>(h, dev, stage, st);
+}
+
+}  // namespace dgc

@@ -149,4 +149,40 @@ __device__ __forceinline__ T rusanov_component(const T *uL, const T *uR, const T
     return T(0.5) * (aL * unl + aR * unr + (pl + pr) * n_r) - T(0.5) * lam * (ownR - ownL);
 }
 
+// All components of the Rusanov flux, each rounded as rusanov_component
+// rounds it in the lane that owns it (there the pressure joins the energy as
+// a rounded value: pl and pr are held back from a fused multiply-add here).
+template <int DIM, class T>
+__device__ __forceinline__ void rusanov_components(const T *uL, const T *uR, const T *n, T *F) {
+    constexpr int M = DIM + 2;
+    const T g1 = T(kGamma - 1.0);
+    const T irl = dev_recip<T>(uL[0]), irr = dev_recip<T>(uR[0]);
+    T unl = 0, unr = 0, kel = 0, ker = 0;
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+        unl += uL[1 + d] * n[d];
+        unr += uR[1 + d] * n[d];
+        kel += uL[1 + d] * uL[1 + d];
+        ker += uR[1 + d] * uR[1 + d];
+    }
+    unl *= irl;
+    unr *= irr;
+    const T pl = g1 * (uL[M - 1] - T(0.5) * kel * irl);
+    const T pr = g1 * (uR[M - 1] - T(0.5) * ker * irr);
+    const T cl = dev_sqrt<T>(T(kGamma) * pl * irl);
+    const T cr = dev_sqrt<T>(T(kGamma) * pr * irr);
+    const T al = (unl < 0 ? -unl : unl) + cl;
+    const T ar = (unr < 0 ? -unr : unr) + cr;
+    const T lam = al > ar ? al : ar;
+    T rl = pl, rr = pr;
+    asm("" : "+v"(rl), "+v"(rr));
+#pragma unroll
+    for (int r = 0; r < M; ++r) {
+        const T aL = r == M - 1 ? uL[r] + rl : uL[r], aR = r == M - 1 ? uR[r] + rr : uR[r];
+        T s = aL * unl + aR * unr;
+        if (r > 0 && r <= DIM) s += (pl + pr) * n[r - 1];
+        F[r] = T(0.5) * s - T(0.5) * lam * (uR[r] - uL[r]);
+    }
+}
+
 }  // namespace dgc_dev

@@ -3,8 +3,9 @@
 Times every candidate launch configuration (kernel form, work-group size,
 XCD remapping) of one device mesh on the caller's data with HIP events and
 installs the fastest one; then, optionally, the fastest SSP-RK3 step
-schedule (volume term and stage combination fused into the first and last
-colors' launches, the combination only, or separate launches).  All
+schedule (the library's default, the volume term and stage combination fused
+into the first and last colors' launches, the combination only, or separate
+launches).  All
 candidates compute the same result; only the rounding order of some sums
 could differ between forms, and every form is bitwise deterministic.
 """
@@ -66,7 +67,7 @@ def autotune(dmesh, U, rhs, variant: str = "colored", precision: str = "f64", ca
     return best, results
 
 
-RK_FORMS = ("fused_volume", "fused", "separate")
+RK_FORMS = ("default", "fused_volume", "fused", "separate")
 
 
 def autotune_rk(dmesh, U, dt: float, precision: str = "f64", forms=RK_FORMS, reps: int = 5, warmup: int = 2):

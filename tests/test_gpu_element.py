@@ -1,0 +1,204 @@
+"""The one-pass element stage (DGC_RK_DEFAULT) against the oracle's step and
+the colored schedules: sizes around a work-group's share of elements, every
+element type and order, walls, hanging faces, more colors than faces, calls
+that fall back to the colored launches, batches."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import synth
+from oracle import dg
+from oracle.mesh import build_mesh
+from tests.helpers import make_input
+
+dgc = pytest.importorskip("paper_1601_07613_amd")
+
+pytestmark = pytest.mark.gpu
+
+
+def _setup(kind, size, p, seed=1, layout="paper", algorithm="paper", with_slots=True):
+    import torch
+
+    m = make_input(kind, size, seed)
+    M = dgc.Mesh.build(m["elem_vert"], m["elem_xyz"])
+    M.color(seed=seed, layout=layout, algorithm=algorithm)
+    D = dgc.DeviceMesh(M, p, with_slots=with_slots)
+    d = dg.Discretization(build_mesh(m["elem_vert"], m["elem_xyz"]), p)
+    ev = m["elem_vert"] if m["elem_vert"].shape[1] == 4 and D.dim == 2 else None
+    cen = synth.element_centroid(m["elem_xyz"], ev)
+    st = synth.density_wave_states(cen) if D.dim == 3 else synth.density_wave_states(cen, vel=(0.5, 0.3))
+    U0 = synth.perturbed_dofs(d.mesh.elem_measure, st, D.n_p, eps=0.01, seed=seed)
+    if kind.startswith("hybrid"):
+        U0[m["elem_vert"][:, 3] < 0, :, (p + 1) * (p + 2) // 2:] = 0.0
+    return D, d, U0, torch.from_numpy(D.to_layout(U0)).cuda()
+
+
+def _steps(D, U0, form, precision="f64", n=3, dt=1e-4):
+    import torch
+
+    D.set_rk_form(form)
+    U = U0.clone()
+    ws = D.workspace("rk", "colored", precision)
+    for _ in range(n):
+        D.rk_step(U, dt, precision=precision, ws=ws)
+    D.set_rk_form("default")
+    torch.cuda.synchronize()
+    return U
+
+
+# K around multiples of the 64 (2D) and 48 (3D) elements of a work-group: 18,
+# 50, 72, 128, 162 triangles; 9..121 parallelograms; 48, 162, 384 tetrahedra
+@pytest.mark.parametrize("kind,size", [("periodic", 3), ("periodic", 5), ("periodic", 6), ("periodic", 8),
+                                       ("periodic", 9), ("delaunay", 400)])
+@pytest.mark.parametrize("p", [0, 1, 2, 3, 4, 5])
+def test_triangles_match_oracle(gpu_device, kind, size, p):
+    D, d, U0, Ug = _setup(kind, size, p)
+    ref = dg.rk3_step(d, U0, 1e-4)
+    got = D.from_layout(_steps(D, Ug, "default", n=1).cpu().numpy())
+    assert np.abs(got - ref).max() <= 1e-12 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("kind,size", [("quads", 4), ("quads", 8), ("quadbox", 9), ("quadbox", 11), ("hybrid", 8),
+                                       ("hybridbox", 9)])
+@pytest.mark.parametrize("p", [0, 1, 2, 3])
+def test_quads_and_mixed_match_oracle(gpu_device, kind, size, p):
+    D, d, U0, Ug = _setup(kind, size, p)
+    ref = dg.rk3_step(d, U0, 1e-4)
+    got = D.from_layout(_steps(D, Ug, "default", n=1).cpu().numpy())
+    assert np.abs(got - ref).max() <= 1e-12 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("kind,size", [("tetbox", 2), ("tets", 3), ("tets", 4), ("tetbox", 5)])
+@pytest.mark.parametrize("p", [0, 1, 2])
+def test_tetrahedra_match_oracle(gpu_device, kind, size, p):
+    D, d, U0, Ug = _setup(kind, size, p)
+    ref = dg.rk3_step(d, U0, 1e-4)
+    got = D.from_layout(_steps(D, Ug, "default", n=1).cpu().numpy())
+    assert np.abs(got - ref).max() <= 1e-12 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("kind,size,p", [("delaunay", 6000, 1), ("delaunay", 6000, 2), ("periodic", 33, 3),
+                                         ("quadbox", 33, 1), ("quadbox", 33, 2), ("quads", 34, 3),
+                                         ("hybridbox", 21, 2), ("delaunay", 900, 5), ("tetbox", 7, 1)])
+@pytest.mark.parametrize("layout", ["paired", "none"])
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+def test_matches_colored_steps(gpu_device, kind, size, p, layout, precision):
+    """Three steps against the colored launches: 1e-14 of the state in f64,
+    1e-5 of the change in f32 (the bars of the other step forms)."""
+    D, d, U0, Ug = _setup(kind, size, p, seed=3, layout=layout)
+    a = _steps(D, Ug, "default", precision)
+    b = _steps(D, Ug, "separate", precision)
+    change = (b - Ug).abs().max().item()
+    assert change > 0
+    tol = 1e-14 * b.abs().max().item() if precision == "f64" else 1e-5 * change
+    assert (a - b).abs().max().item() <= tol
+
+
+def test_f32_rounds_like_the_colored_step(gpu_device):
+    """The f32 form of the element pass keeps the colored kernels' rounding:
+    the same f32 right-hand side, the stage sums in f64."""
+    for kind, size, p in (("delaunay", 3000, 1), ("delaunay", 3000, 2), ("periodic", 20, 3), ("quadbox", 21, 2)):
+        D, d, U0, Ug = _setup(kind, size, p, seed=5)
+        a, b = _steps(D, Ug, "default", "f32"), _steps(D, Ug, "fused_volume", "f32")
+        assert (a - b).abs().max().item() <= 1e-14 * b.abs().max().item(), (kind, p)
+
+
+def test_more_colors_than_faces_and_no_slots(gpu_device):
+    """A greedy coloring (up to five colors) takes the element pass in f64;
+    without the element -> face slots the colored launches run."""
+    D, d, U0, Ug = _setup("delaunay", 900, 2, algorithm="greedy")
+    assert D.info["n_colors"] > 3
+    N, _, _, Un = _setup("delaunay", 900, 2, algorithm="greedy", with_slots=False)
+    a, b = _steps(D, Ug, "default"), _steps(N, Un, "default")
+    assert (a - b).abs().max().item() <= 1e-14 * b.abs().max().item()
+    # f32: the colored launches, as before
+    a, b = _steps(D, Ug, "default", "f32"), _steps(D, Ug, "separate", "f32")
+    assert (a - b).abs().max().item() <= 1e-14 * b.abs().max().item()
+
+
+@pytest.mark.parametrize("p", [0, 1, 2, 3, 4, 5])
+def test_hanging_faces(gpu_device, p):
+    """Two refinement passes (up to six face slots): against the separate launches."""
+    import torch
+
+    m = synth.periodic_tri(8, seed=4)
+    M = dgc.Mesh.build(m["elem_vert"], m["elem_xyz"])
+    M.color(seed=0)
+    for level in range(2):
+        info = M.info()
+        xyz = M.export("elem_xyz").reshape(info["n_elem"], 3, 2)
+        M, _ = M.refine(synth.refine_flags(xyz, M.export("elem_level"), level, radius=0.3))
+    D = dgc.DeviceMesh(M, p)
+    assert D.info["max_slots"] > 3
+    xyz = M.export("elem_xyz").reshape(D.K, 3, 2)
+    st = synth.density_wave_states(synth.element_centroid(xyz), vel=(0.5, 0.3))
+    U0 = synth.perturbed_dofs(synth.element_measure(xyz), st, D.n_p, eps=0.01, seed=2)
+    Ug = torch.from_numpy(D.to_layout(U0)).cuda()
+    for precision in ("f64", "f32"):
+        a, b = _steps(D, Ug, "default", precision), _steps(D, Ug, "separate", precision)
+        assert (a - b).abs().max().item() <= 1e-14 * b.abs().max().item(), precision
+
+
+def test_malformed_faces_are_skipped(gpu_device):
+    """Face ids, codes and slots out of range contribute nothing to the
+    elements that would read through them and are never dereferenced."""
+    import torch
+
+    D, d, U0, Ug = _setup("delaunay", 900, 2)
+    E, own = D.E, [40]
+    # the colored launches drop a face with an id out of range on both sides
+    # and do not read the slots: those elements are left out
+    own += [int(D.face_lr[3]), int(D.face_lr[E + 10])]
+    D.face_lr[3] = D.K               # left element of face 3
+    D.face_lr[E + 10] = D.K + 5      # right element of face 10
+    D.face_code[20] = 200            # left code of face 20
+    D.face_code[E + 30] = 99         # right code of face 30
+    slot = int(D.elem_slots[40])
+    D.elem_slots[40] = 2 * E         # a slot beyond the faces
+    a = _steps(D, Ug, "default", n=1)
+    D.elem_slots[40] = slot
+    b = _steps(D, Ug, "separate", n=1)
+    assert torch.isfinite(a).all()
+    # a step's three stages carry a difference to the third ring of neighbours
+    skip = torch.zeros(D.K, dtype=torch.bool, device="cuda")
+    skip[own] = True
+    lr = D.face_lr.view(2, E).long()
+    ok = ((lr >= 0) & (lr < D.K)).all(dim=0)
+    L, R = lr[0][ok], lr[1][ok]
+    for _ in range(3):
+        grow = skip.clone()
+        grow[L[skip[R]]] = True
+        grow[R[skip[L]]] = True
+        skip = grow
+    keep = ~skip
+    assert int(keep.sum()) > D.K // 2
+    assert (a - b)[keep].abs().max().item() <= 1e-14 * b.abs().max().item()
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+def test_batch_with_refined_member(gpu_device, precision):
+    """A batch of conforming and refined members steps each like its single-mesh step."""
+    import torch
+
+    members, ref = [], []
+    for n, refine in ((9, False), (6, True), (17, False)):
+        m = synth.periodic_tri(n, seed=n)
+        M = dgc.Mesh.build(m["elem_vert"], m["elem_xyz"])
+        M.color(seed=0)
+        if refine:
+            M, _ = M.refine((np.arange(2 * n * n) % 7 == 0).astype(np.uint8))
+        D = dgc.DeviceMesh(M, 2)
+        xyz = M.export("elem_xyz").reshape(D.K, 3, 2)
+        st = synth.density_wave_states(synth.element_centroid(xyz), vel=(0.5, 0.3))
+        U = torch.from_numpy(D.to_layout(synth.perturbed_dofs(synth.element_measure(xyz), st, 6, seed=n))).cuda()
+        members.append((D, U, D.workspace("rk", "colored", precision), 1e-4))
+        ref.append((D, U.clone()))
+    B = dgc.Batch(members, precision=precision)
+    for _ in range(3):
+        B.rk_step()
+    torch.cuda.synchronize()
+    for (D, U, _, _), (_, U0) in zip(members, ref):
+        b = _steps(D, U0, "default", precision)
+        tol = 1e-14 * b.abs().max().item() if precision == "f64" else 1e-5 * (b - U0).abs().max().item()
+        assert (U - b).abs().max().item() <= tol
