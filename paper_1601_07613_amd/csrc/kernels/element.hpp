@@ -102,22 +102,38 @@ struct ElemCfg {
     static constexpr int plane(int fg) { return (EW * fg * Q) | 1; }
     static constexpr int gplane(int fg) { return (EW * fg) | 1; }
     static constexpr int group_len(int fg) { return 2 * M * plane(fg) + NG * gplane(fg); }
-    // face slots per group: what keeps the wave's region within 11 KB (three
-    // waves per SIMD); all four sides at N_p = 9 (15 KB: the registers leave
-    // two waves anyway; 589,824 parallelograms 234 us a stage, with three
-    // sides and one 260); one at N_p >= 16 (two sides' modes do not fit the
-    // registers: 39,762 triangles at p = 5 94 us, with two 162)
-    static constexpr int BUDGET = (NP >= 16 ? 7 : (NP == 9 && !PROJ && !MIXED ? 15 : 11)) * 1024;
-    static constexpr int fit(int fg) { return fg <= 1 || group_len(fg) * (int)sizeof(T) <= BUDGET ? fg : fit(fg - 1); }
-    static constexpr int FG = fit(FS);
+    // Face slots per group: one; where a side has two points (2 * 16 fill half
+    // a wave) two, and all three of a triangle; two for triangles at p = 2;
+    // f32 below N_p = 9 all.  Fewer sides at a time leave the flux's share of
+    // a wave's lanes the same at three and four points (three sides: 144
+    // points in three rounds of 64; one: 48 in one) and take fewer registers
+    // and less LDS: 131 registers and three waves per SIMD with three sides,
+    // 128 and four with two (991,232 triangles at p = 2: 226 against 219 us a
+    // stage; 589,824 parallelograms at p = 2 234 with four sides, 217 with
+    // one, before the late x read below).
+    static constexpr int FG = PROJ ? (NP >= 9 || FS > 4 ? 1 : FS)
+                              : NP == 3 && FS == 3 ? 3
+                              : Q == 2 || (NP == 6 && FS == 3) ? 2 : 1;
+    // Each group's reads are issued before the work on the group ahead of it
+    // where the registers leave two or three waves either way (39,762
+    // triangles at p = 5: 85 against 93 us, 511,104 tetrahedra at p = 1: 181
+    // against 190); below, they would cost a fourth wave, which hides more.
+    static constexpr bool AHEAD = NP >= 10 || M == 5;
     // the volume term by register exchanges of the team of four lanes, or
     // (M = 5) through the region, QC points at a time; through the region for
-    // M = 4 too took 236 instead of 231 us on 991,232 triangles at p = 2
+    // M = 4 too took 2 % longer on 991,232 triangles at p = 2
     static constexpr bool VTEAM = M == 4;
-    static constexpr int vplane(int qc) { return (EW * qc) | 1; }
-    static constexpr int vfit(int qc) { return qc <= 1 || M * DIM * vplane(qc) <= group_len(FG) ? qc : vfit(qc - 1); }
-    static constexpr int QC = vfit(QV);
-    static constexpr int REGION = group_len(FG) > M * DIM * vplane(QC) ? group_len(FG) : M * DIM * vplane(QC);
+    // f64 triangles at p = 1: two volume points per trip of the team's loop,
+    // and the tables staged before the element's own reads (the other orders
+    // stage them behind these).  512 triangles, bound by latency: 17.4, with
+    // two points 16.6, with both 16.3 us a step; 991,232: 410 us either way.
+    static constexpr bool SMALL = NP == 3 && !PROJ;
+    static constexpr int UNR = SMALL ? 2 : team_volume_unroll(NP);
+    static constexpr int QC = QV < 4 ? QV : (QV % 4 == 0 ? 4 : 5);   // 48 or 60 of the 64 lanes
+    static constexpr int VLEN = VTEAM ? 0 : M * DIM * ((EW * QC) | 1);
+    static constexpr int REGION = group_len(FG) > VLEN ? group_len(FG) : VLEN;
+    // volume points evaluated while the sides are read
+    static constexpr int QH = VTEAM ? QV / 3 : QV / 3 / QC * QC > 0 ? QV / 3 / QC * QC : (QV > QC ? QC : 0);
     __host__ __device__ static constexpr int tab_len(int n_codes) {
         return PROJ ? 2 * n_codes * Q * NP : n_codes * Q * NP + Q;
     }
@@ -129,17 +145,18 @@ struct ElemCfg {
     }
 };
 
-// Volume term of M = 5 variables through the wave's LDS region: the point
-// values are exchanged, each point's flux is evaluated once.
-template <int DIM, int NP, int QV, int QC, int EW, class T>
+// Volume term of M = 5 variables at the points [Q0, Q1) through the wave's
+// LDS region: the point values are exchanged, each point's flux is evaluated
+// once.
+template <int DIM, int NP, int QV, int QC, int EW, int Q0, int Q1, class T>
 __device__ __forceinline__ void volume_wave(int lane, int e, int m, bool lane_ok, const T (&Ji)[DIM * DIM], T isq,
                                             const double *__restrict__ vb, const double *__restrict__ vd,
                                             const T (&c)[NP], T *region, T (&acc)[NP]) {
     constexpr int M = DIM + 2;
     constexpr int P = (EW * QC) | 1;
 #pragma unroll 1
-    for (int q0 = 0; q0 < QV; q0 += QC) {
-        const int nq = QV - q0 < QC ? QV - q0 : QC;
+    for (int q0 = Q0; q0 < Q1; q0 += QC) {
+        const int nq = Q1 - q0 < QC ? Q1 - q0 : QC;
         if (lane_ok) {
 #pragma unroll 2
             for (int q = 0; q < nq; ++q) {
@@ -197,10 +214,11 @@ __device__ __forceinline__ int point_place(int o, int q) {
 
 // The stage of the EPB elements from k0 on (every thread of the work-group
 // calls; s_tab holds the trace tables, the face weights or projection tables,
-// then on mixed meshes the volume tables).
-template <int DIM, int NP, int Q, int QV, int FS, bool MIXED, class T>
+// then on mixed meshes the volume tables).  `mid` stages the tables and meets
+// the work-group barrier.
+template <int DIM, int NP, int Q, int QV, int FS, bool MIXED, class T, class Mid>
 __device__ __forceinline__ void element_stage(const ElemStageArgs &A, const ElemTables &tab, int64_t k0, int ms,
-                                              const T *s_tab, T *s_regions) {
+                                              const T *s_tab, T *s_regions, const Mid &mid) {
     using C = ElemCfg<DIM, NP, Q, QV, FS, MIXED, T>;
     constexpr int M = C::M, EW = C::EW, FG = C::FG;
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
@@ -213,6 +231,7 @@ __device__ __forceinline__ void element_stage(const ElemStageArgs &A, const Elem
     const T *s_tr = s_tab, *s_w = s_tab + nc * Q * NP;  // weights (f64) or projection tables (f32)
     T *region = s_regions + wave * C::REGION;
 
+    if constexpr (C::SMALL) mid();
     int32_t slot[FS];
 #pragma unroll
     for (int s = 0; s < FS; ++s) slot[s] = s < ms ? A.slots[(int64_t)s * K + kc] : -1;
@@ -225,7 +244,8 @@ __device__ __forceinline__ void element_stage(const ElemStageArgs &A, const Elem
     load_elem_geo<DIM, T>(kc, K, A.elem_geo, Ji, sq);
     const int kind = MIXED ? (A.kind[kc] ? 1 : 0) : 0;
 
-    // the sides: neighbour (-1 where there is none), codes; conditions joined
+    if constexpr (!C::SMALL) mid();
+    // the sides: neighbour (-1 where there is none), codes; read and checked
     // without branches, so that the reads of all sides are in flight together
     int32_t nb[FS];
     int co[FS], cn[FS];
@@ -234,14 +254,45 @@ __device__ __forceinline__ void element_stage(const ElemStageArgs &A, const Elem
 #pragma unroll
     for (int i = 0; i < FS; ++i) {
         const uint32_t sl = (uint32_t)slot[i];
-        const bool in = sl < E2;
-        const uint32_t f = in ? sl >> 1 : 0u;
+        const uint32_t f = sl < E2 ? sl >> 1 : 0u;
         const bool right = sl & 1;
         nb[i] = A.face_lr[(right ? 0 : E) + f];
         co[i] = A.face_code[(right ? E : 0) + f];
         cn[i] = A.face_code[(right ? 0 : E) + f];
+    }
+    // the volume term at the points [Q0, Q1), without its factor sqrt(det J)
+    T c[NP], acc[NP];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+        c[j] = T(yv[j]);
+        acc[j] = T(0);
+    }
+    const double isq_d = sizeof(T) == 8 ? exact_recip(sq) : 1.0 / sq;
+    const T isq = T(isq_d);
+    auto volume = [&](auto first, auto end) {
+        constexpr int Q0 = decltype(first)::value, Q1 = decltype(end)::value;
+        if constexpr (!C::VTEAM) {
+            volume_wave<DIM, NP, QV, C::QC, EW, Q0, Q1, T>(lane, e, m, lane_ok, Ji, isq, tab.vb, tab.vd, c, region,
+                                                           acc);
+        } else if constexpr (MIXED) {
+            const T *s_vb = s_tab + C::tab_len(nc);
+            const T *s_vd = s_vb + 2 * QV * NP;
+            volume_team_points<DIM, NP, QV, Q0, Q1, T>(m, Ji, isq, s_vb + kind * QV * NP, s_vd + kind * DIM * QV * NP, c,
+                                                       acc);
+        } else {
+            volume_team_points<DIM, NP, QV, Q0, Q1, T, double, C::UNR>(m, Ji, isq, tab.vb, tab.vd, c, acc);
+        }
+    };
+    constexpr int QH = C::QH;
+    // the first half of the points covers the reads of the sides, the second
+    // half those of the neighbours' records
+    volume(std::integral_constant<int, 0>{}, std::integral_constant<int, QH>{});
+
+#pragma unroll
+    for (int i = 0; i < FS; ++i) {
         // a malformed face (ids or codes out of range) is skipped, never dereferenced
-        ok[i] = lane_ok & in & (nb[i] < K) & (co[i] < nc) & (cn[i] < nc) & ((nb[i] >= 0) | !right);
+        ok[i] = lane_ok & ((uint32_t)slot[i] < E2) & (nb[i] < K) & (co[i] < nc) & (cn[i] < nc) &
+                ((nb[i] >= 0) | !(slot[i] & 1));
         nb[i] = ok[i] ? nb[i] : -1;
         co[i] = ok[i] ? co[i] : 0;
         cn[i] = ok[i] ? cn[i] : 0;
@@ -277,96 +328,84 @@ __device__ __forceinline__ void element_stage(const ElemStageArgs &A, const Elem
         }
     }
 
-    T c[NP], acc[NP];
-#pragma unroll
-    for (int j = 0; j < NP; ++j) {
-        c[j] = T(yv[j]);
-        acc[j] = T(0);
-    }
-    const double isq_d = sizeof(T) == 8 ? exact_recip(sq) : 1.0 / sq;
-    const T isq = T(isq_d);
-
-    // the stage-0 state of the combination, read up front: it arrives while
-    // the stage is computed (N_p >= 15: at the end, the registers run out)
-    constexpr bool LATE_X = NP >= 15;
+    // The stage-0 state of the combination (the element's own record again
+    // where the combination has none).  f32, bound by memory: not read where
+    // there is none (500,000 triangles at p = 2: 303 against 316 us a step);
+    // f64: without that branch, up front for small records, at the end from
+    // N_p = 6 on, where its registers cost a wave (589,824 parallelograms at
+    // p = 2: 622 against 648 us a step, 991,232 triangles at p = 1 414 late
+    // against 403 early).
+    constexpr bool LATE_X = C::PROJ ? NP >= 15 : M == 4 && NP > 4;
     double xv[NP];
     auto read_x = [&]() {
-        if (A.x) {
+        if constexpr (C::PROJ) {
+            if (A.x) {
 #pragma unroll
-            for (int j = 0; j < NP; ++j) xv[j] = A.x[base + j];
+                for (int j = 0; j < NP; ++j) xv[j] = A.x[base + j];
+            } else {
+#pragma unroll
+                for (int j = 0; j < NP; ++j) xv[j] = yv[j];
+            }
         } else {
+            const double *xp = (A.x ? A.x : A.y) + base;
 #pragma unroll
-            for (int j = 0; j < NP; ++j) xv[j] = yv[j];
+            for (int j = 0; j < NP; ++j) xv[j] = xp[j];
         }
     };
     if constexpr (!LATE_X) read_x();
 
-    // volume term, without its factor sqrt(det J) where the first slot applies
-    // it (the first group's neighbour reads are in flight by then)
-    const double vsq = C::VFUSED ? 1.0 : sq;
-    auto volume = [&]() {
-        if constexpr (C::VTEAM) {
-            if constexpr (MIXED) {
-                const T *s_vb = s_tab + C::tab_len(nc);
-                const T *s_vd = s_vb + 2 * QV * NP;
-                volume_team_core_geo<DIM, NP, QV, T, T>(m, Ji, vsq, isq_d, s_vb + kind * QV * NP,
-                                                        s_vd + kind * DIM * QV * NP, c, acc);
-            } else {
-                volume_team_core_geo<DIM, NP, QV, T, double>(m, Ji, vsq, isq_d, tab.vb, tab.vd, c, acc);
-            }
-        } else {
-            volume_wave<DIM, NP, QV, C::QC, EW, T>(lane, e, m, lane_ok, Ji, isq, tab.vb, tab.vd, c, region, acc);
+    // a group's reads: the neighbours' records (the element's own where there
+    // is none), and the geometry of side i by lane m = i of the element
+    struct Sides {
+        T nb[FG][NP];
+        double geo[C::NG];
+    };
+    static_assert(FG <= M, "a lane of the element for every side of a group");
+    auto read_group = [&](auto first, Sides &v) {
+        constexpr int s0 = decltype(first)::value;
+        uint32_t sl = 0;
 #pragma unroll
-            for (int j = 0; j < NP; ++j) acc[j] *= T(vsq);
+        for (int i = 0; i < FG && s0 + i < FS; ++i) sl = (i == m) & ok[s0 + i] ? (uint32_t)slot[s0 + i] : sl;
+        const double *fg = A.face_geo + (sl >> 1);
+#pragma unroll
+        for (int d = 0; d <= DIM; ++d) v.geo[d] = fg[d * E];
+        v.geo[DIM + 1] = fg[(DIM + ((sl & 1) ? 1 : 2)) * E];
+#pragma unroll
+        for (int i = 0; i < FG && s0 + i < FS; ++i) {
+            const int64_t b = nb[s0 + i] >= 0 ? nb[s0 + i] : kc;
+            const double *u = A.y + ((size_t)b * M + m) * NP;
+#pragma unroll
+            for (int j = 0; j < NP; ++j) v.nb[i][j] = T(u[j]);
         }
     };
+    Sides sides0;
+    read_group(std::integral_constant<int, 0>{}, sides0);
+    volume(std::integral_constant<int, QH>{}, std::integral_constant<int, QV>{});
+    if constexpr (!C::VFUSED) {
+#pragma unroll
+        for (int j = 0; j < NP; ++j) acc[j] *= T(sq);
+    }
 
     // one group of face slots
-    auto group = [&](auto first) {
+    auto group = [&](auto first, const Sides &v) {
         constexpr int s0 = decltype(first)::value;
         constexpr int G = FS - s0 < FG ? FS - s0 : FG;
         constexpr int P = C::plane(G), GP = C::gplane(G);
         T *s_own = region, *s_nb = region + M * P, *s_geo = region + 2 * M * P;
-        // lane m of an element reads the geometry of its group's sides m, m + M
-        constexpr int GS = (G + M - 1) / M;
-        double gv[GS][C::NG];
-        bool gok[GS], gright[GS], gwall[GS];
+        if (lane_ok && m < G) {
+            bool right = slot[s0] & 1, wall = nb[s0] < 0;
 #pragma unroll
-        for (int g = 0; g < GS; ++g) {
-            uint32_t sl = 0;
-            gok[g] = gwall[g] = false;
-#pragma unroll
-            for (int i = 0; i < G; ++i) {
-                    const bool mine = i == g * M + m;
-                sl = mine & ok[s0 + i] ? (uint32_t)slot[s0 + i] : sl;
-                gok[g] = gok[g] | (mine & ok[s0 + i]);
-                gwall[g] = gwall[g] | (mine & (nb[s0 + i] < 0));
+            for (int i = 1; i < G; ++i) {
+                right = i == m ? slot[s0 + i] & 1 : right;
+                wall = i == m ? nb[s0 + i] < 0 : wall;
             }
-            gright[g] = sl & 1;
-            const double *fg = A.face_geo + (sl >> 1);
+            T *q = s_geo + e * G + m;
 #pragma unroll
-            for (int d = 0; d <= DIM; ++d) gv[g][d] = fg[d * E];
-            gv[g][DIM + 1] = fg[(DIM + (gright[g] ? 1 : 2)) * E];
-        }
-        T cnb[G][NP];
-#pragma unroll
-        for (int i = 0; i < G; ++i) {
-            const int64_t b = nb[s0 + i] >= 0 ? nb[s0 + i] : kc;
-            const double *u = A.y + ((size_t)b * M + m) * NP;
-#pragma unroll
-            for (int j = 0; j < NP; ++j) cnb[i][j] = T(u[j]);
-        }
-        if (s0 == 0) volume();
-#pragma unroll
-        for (int g = 0; g < GS; ++g) {
-            if (!gok[g]) continue;
-            T *q = s_geo + e * G + g * M + m;
-#pragma unroll
-            for (int d = 0; d < DIM; ++d) q[d * GP] = T(gv[g][d]);
-            q[DIM * GP] = T(C::PROJ ? gv[g][DIM] * isq_d : gv[g][DIM]);
+            for (int d = 0; d < DIM; ++d) q[d * GP] = T(v.geo[d]);
+            q[DIM * GP] = T(C::PROJ ? v.geo[DIM] * isq_d : v.geo[DIM]);
             // negative: this element is the face's right one; 0: wall
-            const T is = gwall[g] ? T(0) : T(gv[g][DIM + 1]);
-            q[(DIM + 1) * GP] = gright[g] ? -is : is;
+            const T is = wall ? T(0) : T(v.geo[DIM + 1]);
+            q[(DIM + 1) * GP] = right ? -is : is;
         }
         wave_lds_fence();
 #pragma unroll
@@ -382,7 +421,7 @@ __device__ __forceinline__ void element_stage(const ElemStageArgs &A, const Elem
 #pragma unroll
                 for (int j = 0; j < NP; ++j) {
                     t += (C::FACES ? T(tab.trace[(s * C::NO * Q + q) * NP + j]) : to[q * NP + j]) * c[j];
-                    u += tn[q * NP + j] * cnb[i][j];
+                    u += tn[q * NP + j] * v.nb[i][j];
                 }
                 po[C::FACES ? point_place<DIM, Q>(co[s], q) : q] = t * isq;
                 pn[q] = u * isn;
@@ -461,9 +500,19 @@ __device__ __forceinline__ void element_stage(const ElemStageArgs &A, const Elem
         }
         if constexpr (s0 + FG < FS) wave_lds_fence();
     };
-    [&]<int... I>(std::integer_sequence<int, I...>) {
-        (group(std::integral_constant<int, I * FG>{}), ...);
-    }(std::make_integer_sequence<int, (FS + FG - 1) / FG>{});
+    auto groups = [&](auto &self, auto first, const Sides &cur) -> void {
+        constexpr int s0 = decltype(first)::value;
+        if constexpr (s0 + FG < FS) {
+            Sides next;
+            if constexpr (C::AHEAD) read_group(std::integral_constant<int, s0 + FG>{}, next);
+            group(first, cur);
+            if constexpr (!C::AHEAD) read_group(std::integral_constant<int, s0 + FG>{}, next);
+            self(self, std::integral_constant<int, s0 + FG>{}, next);
+        } else {
+            group(first, cur);
+        }
+    };
+    groups(groups, std::integral_constant<int, 0>{}, sides0);
     if (!lane_ok) return;
     if constexpr (LATE_X) read_x();
 #pragma unroll
@@ -495,14 +544,25 @@ __device__ __forceinline__ void stage_elem_tables(T *s, const ElemTables &tab) {
     __syncthreads();
 }
 
+// Work-groups are dealt round-robin to the 8 XCDs: give each XCD runs of
+// CHUNK consecutive work-groups, whose neighbours' records then sit in its
+// own L2 (the last, incomplete round stays as it is): a stage on 991,232
+// triangles at p = 2 fetches 547 instead of 750 MB, on 511,104 tetrahedra at
+// p = 1 it takes 183 instead of 193 us.
+__device__ __forceinline__ unsigned chunked_block(unsigned b, unsigned nb) {
+    constexpr unsigned CHUNK = 32;
+    const unsigned first = b / (8 * CHUNK) * (8 * CHUNK), r = b - first;
+    return first + 8 * CHUNK > nb ? b : first + r % 8 * CHUNK + r / 8;
+}
+
 template <int DIM, int NP, int Q, int QV, int FS, bool MIXED, class T>
 __global__ __launch_bounds__((ElemCfg<DIM, NP, Q, QV, FS, MIXED, T>::BLOCK)) void element_stage_kernel(ElemStageArgs A, ElemTables tab, int ms) {
     using C = ElemCfg<DIM, NP, Q, QV, FS, MIXED, T>;
     extern __shared__ unsigned char smem_raw[];
     T *s_tab = reinterpret_cast<T *>(smem_raw);
-    stage_elem_tables<DIM, NP, Q, QV, FS, MIXED, T>(s_tab, tab);
-    element_stage<DIM, NP, Q, QV, FS, MIXED, T>(A, tab, (int64_t)blockIdx.x * C::EPB, ms, s_tab,
-                                                s_tab + C::tab_len(tab.n_codes) + C::VTAB);
+    element_stage<DIM, NP, Q, QV, FS, MIXED, T>(A, tab, (int64_t)chunked_block(blockIdx.x, gridDim.x) * C::EPB, ms, s_tab,
+                                                s_tab + C::tab_len(tab.n_codes) + C::VTAB,
+                                                [&] { stage_elem_tables<DIM, NP, Q, QV, FS, MIXED, T>(s_tab, tab); });
 }
 
 // The stage of every mesh of a batch: a work-group finds its mesh in the
@@ -516,8 +576,8 @@ __global__ __launch_bounds__((ElemCfg<DIM, NP, Q, QV, FS, MIXED, T>::BLOCK)) voi
     const double *tables = gptr(h->tables);
     const ElemTables tab{tables + h->off_trace, tables + h->off_proj, tables + h->off_vb, tables + h->off_vd,
                          h->n_codes};
-    stage_elem_tables<DIM, NP, Q, QV, FS, MIXED, T>(s_tab, tab);
-    const int32_t i = reinterpret_cast<const int32_t *>(desc + h->off_map_stage)[blockIdx.x];
+    const unsigned b = chunked_block(blockIdx.x, gridDim.x);
+    const int32_t i = reinterpret_cast<const int32_t *>(desc + h->off_map_stage)[b];
     const Entry *en = bentry(desc, i);
     const Member mb = member(en, sizeof(T) == 4);
     ElemStageArgs A;
@@ -538,8 +598,9 @@ __global__ __launch_bounds__((ElemCfg<DIM, NP, Q, QV, FS, MIXED, T>::BLOCK)) voi
     A.a = stage == 0 ? 0.0 : (stage == 1 ? 0.75 : 1.0 / 3.0);
     A.b = stage == 0 ? 1.0 : (stage == 1 ? 0.25 : 2.0 / 3.0);
     A.dt = en->dt;
-    element_stage<DIM, NP, Q, QV, FS, MIXED, T>(A, tab, ((int64_t)blockIdx.x - en->blk_stage) * C::EPB, en->max_slots,
-                                                s_tab, s_tab + C::tab_len(tab.n_codes) + C::VTAB);
+    element_stage<DIM, NP, Q, QV, FS, MIXED, T>(A, tab, ((int64_t)b - en->blk_stage) * C::EPB, en->max_slots,
+                                                s_tab, s_tab + C::tab_len(tab.n_codes) + C::VTAB,
+                                                [&] { stage_elem_tables<DIM, NP, Q, QV, FS, MIXED, T>(s_tab, tab); });
 }
 
 }  // namespace dgc_dev

@@ -54,29 +54,22 @@ __device__ __forceinline__ void load_elem_geo(int64_t k, int64_t n_elem, const d
     sq = elem_geo[DIM * DIM * n_elem + k];
 }
 
-// Lane r's share of an element's volume term from its geometry (Ji, sq and
-// inv_sq = 1 / sq, the value a face record already carries): c
-// holds the element's modes of variable r (zeros on lanes r >= M), out
-// receives the result for variable r (all lanes of the team must call; the
-// tables may live in global memory (f64) or in LDS).
-template <int DIM, int NP, int QV, class T, class TAB = double, int UNR = team_volume_unroll(NP)>
-__device__ __forceinline__ void volume_team_core_geo(int r, const T (&Ji)[DIM * DIM], double sq, double inv_sq,
-                                                     const TAB *__restrict__ vb, const TAB *__restrict__ vd,
-                                                     const T (&c)[NP], T (&out)[NP]) {
+// Lane r's share of an element's volume term at the points [Q0, Q1) of QV,
+// added to acc without the factor sqrt(det J) (isq = 1/sqrt(det J)); all
+// lanes of the team must call.
+template <int DIM, int NP, int QV, int Q0, int Q1, class T, class TAB, int UNR = team_volume_unroll(NP)>
+__device__ __forceinline__ void volume_team_points(int r, const T (&Ji)[DIM * DIM], T isq, const TAB *__restrict__ vb,
+                                                   const TAB *__restrict__ vd, const T (&c)[NP], T (&acc)[NP]) {
     constexpr int M = DIM + 2;
     constexpr int TEAM = volume_team_size<DIM>();
-    const T isq = T(inv_sq);
     // this lane's share of the physical flux F_r(u) = a u_e / rho + [r = 1 + e] p,
     // a = u_r (+ p for the energy): 0/1 selectors fixed per lane
     const T sel_e = r == M - 1 ? T(1) : T(0);
     T sel_m[DIM];
 #pragma unroll
     for (int e = 0; e < DIM; ++e) sel_m[e] = r == 1 + e ? T(1) : T(0);
-    T acc[NP];
-#pragma unroll
-    for (int j = 0; j < NP; ++j) acc[j] = 0;
 #pragma unroll UNR
-    for (int q = 0; q < QV; ++q) {
+    for (int q = Q0; q < Q1; ++q) {
         T t = 0;
 #pragma unroll
         for (int j = 0; j < NP; ++j) t += T(vb[q * NP + j]) * c[j];
@@ -100,6 +93,21 @@ __device__ __forceinline__ void volume_team_core_geo(int r, const T (&Ji)[DIM * 
             for (int d = 0; d < DIM; ++d) acc[j] = dev_fma(T(vd[(d * QV + q) * NP + j]), G[d], acc[j]);
         }
     }
+}
+
+// Lane r's share of an element's volume term from its geometry (Ji, sq and
+// inv_sq = 1 / sq, the value a face record already carries): c
+// holds the element's modes of variable r (zeros on lanes r >= M), out
+// receives the result for variable r (all lanes of the team must call; the
+// tables may live in global memory (f64) or in LDS).
+template <int DIM, int NP, int QV, class T, class TAB = double, int UNR = team_volume_unroll(NP)>
+__device__ __forceinline__ void volume_team_core_geo(int r, const T (&Ji)[DIM * DIM], double sq, double inv_sq,
+                                                     const TAB *__restrict__ vb, const TAB *__restrict__ vd,
+                                                     const T (&c)[NP], T (&out)[NP]) {
+    T acc[NP];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) acc[j] = 0;
+    volume_team_points<DIM, NP, QV, 0, QV, T, TAB, UNR>(r, Ji, T(inv_sq), vb, vd, c, acc);
 #pragma unroll
     for (int j = 0; j < NP; ++j) out[j] = acc[j] * T(sq);
 }
