@@ -140,6 +140,31 @@ def test_hanging_faces(gpu_device, p):
         assert (a - b).abs().max().item() <= 1e-14 * b.abs().max().item(), precision
 
 
+@pytest.mark.parametrize("p", [0, 1, 2, 5])
+@pytest.mark.parametrize("where", [0, 40, 511])
+def test_waves_with_and_without_hanging_faces(gpu_device, p, where):
+    """One refined element: most waves leave the slots from the fourth on out,
+    those beside it do not, also with the empty slots first.  Only the order of
+    an element's six contributions differs between the runs: a few roundings."""
+    import torch
+
+    m = synth.periodic_tri(16, seed=4)
+    M = dgc.Mesh.build(m["elem_vert"], m["elem_xyz"])
+    M.color(seed=0)
+    M, _ = M.refine((np.arange(512) == where).astype(np.uint8))
+    D = dgc.DeviceMesh(M, p)
+    assert D.info["max_slots"] > 3
+    xyz = M.export("elem_xyz").reshape(D.K, 3, 2)
+    st = synth.density_wave_states(synth.element_centroid(xyz), vel=(0.5, 0.3))
+    U0 = synth.perturbed_dofs(synth.element_measure(xyz), st, D.n_p, eps=0.01, seed=2)
+    Ug = torch.from_numpy(D.to_layout(U0)).cuda()
+    a, b = _steps(D, Ug, "default"), _steps(D, Ug, "separate")
+    assert (a - b).abs().max().item() <= 1e-14 * b.abs().max().item()
+    D.elem_slots.copy_(D.elem_slots.view(D.info["max_slots"], D.K).flip(0).reshape(-1))
+    c = _steps(D, Ug, "default")
+    assert (c - b).abs().max().item() <= 1e-14 * b.abs().max().item()
+
+
 def test_malformed_faces_are_skipped(gpu_device):
     """Face ids, codes and slots out of range contribute nothing to the
     elements that would read through them and are never dereferenced."""
