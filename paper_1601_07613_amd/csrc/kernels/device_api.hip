@@ -771,20 +771,26 @@ dgc_status dgc_permute_records(const void *src, void *dst, const int32_t *perm, 
     hipStream_t st = static_cast<hipStream_t>(stream);
     // the widest piece that the record size and both buffers' alignment allow
     const uintptr_t al = reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst) | (uintptr_t)rec_bytes;
-    auto go = [&](auto piece) {
+    auto launch = [&](auto piece, auto index, auto pieces) {
         using V = decltype(piece);
-        const int64_t words = rec_bytes / (int64_t)sizeof(V);
-        const int64_t per_block = kBlock * dgc_dev::kPermutePieces;
+        using I = decltype(index);
+        constexpr int N = decltype(pieces)::value;
+        const int64_t words = rec_bytes / (int64_t)sizeof(V), per_block = kBlock * N;
         const dim3 grid((unsigned)((n_rec * words + per_block - 1) / per_block));
+        hipLaunchKernelGGL((dgc_dev::permute_records_kernel<V, I, N>), grid, dim3(kBlock), 0, st,
+                           static_cast<const V *>(src), static_cast<V *>(dst), perm, (I)n_rec, (I)words,
+                           to_layout ? 1 : 0);
+    };
+    auto go = [&](auto piece) {
+        const int64_t n = n_rec * (rec_bytes / (int64_t)sizeof(piece));
+        // one piece per work-item as long as the chip holds them all at once,
+        // 256 compute units of 2,048 work-items: 3,200 records of 192 bytes
+        // 2.7 us (four pieces: 3.4), 8,192 of 96 bytes 2.9 (3.5), 39,200 of
+        // 192 bytes 4.3 (4.7); beyond, 57,800 of 192 bytes 6.0 (5.6)
+        if (n <= 256 * 2048) launch(piece, uint32_t{}, std::integral_constant<int, 1>{});
         // 32-bit indices as long as the last work-group's stay below 2^32
-        if (n_rec * words <= (int64_t)UINT32_MAX - per_block)
-            hipLaunchKernelGGL((dgc_dev::permute_records_kernel<V, uint32_t>), grid, dim3(kBlock), 0, st,
-                               static_cast<const V *>(src), static_cast<V *>(dst), perm, (uint32_t)n_rec,
-                               (uint32_t)words, to_layout ? 1 : 0);
-        else
-            hipLaunchKernelGGL((dgc_dev::permute_records_kernel<V, int64_t>), grid, dim3(kBlock), 0, st,
-                               static_cast<const V *>(src), static_cast<V *>(dst), perm, n_rec, words,
-                               to_layout ? 1 : 0);
+        else if (n <= (int64_t)UINT32_MAX - 4 * kBlock) launch(piece, uint32_t{}, std::integral_constant<int, 4>{});
+        else launch(piece, int64_t{}, std::integral_constant<int, 4>{});
     };
     if (al % 16 == 0) go(uint4{});
     else if (al % 8 == 0) go(uint2{});

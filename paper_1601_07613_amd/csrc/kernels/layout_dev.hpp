@@ -16,45 +16,45 @@
 namespace dgc_dev {
 
 // Pieces of V bytes (16, 8 or 4: the widest that the record size and both
-// buffers' alignment allow), kPermutePieces per work-item, a work-group's
-// pieces interleaved so that consecutive lanes move consecutive pieces.
+// buffers' alignment allow), N per work-item, a work-group's pieces
+// interleaved so that consecutive lanes move consecutive pieces.
 // Bound by memory: two record passes, one of them scattered by record.
 // Measured into / out of the layout order: 991,232 records of 192 bytes
 // 92 / 70 us (4.1 / 5.4 TB/s), 65,522 of 320 bytes 6.7 / 7.3 us.  With one
 // 4-byte word per work-item and 64-bit index divisions 164 / 166 and
 // 14.2 / 15.0 us; with the reads under a branch per piece, which serialises
-// them, 98 / 82 and 20.2 / 20.2 us; 1, 2 or 8 pieces are within 5 %.
-constexpr int kPermutePieces = 4;
-template <class V, class I>
+// them, 98 / 82 and 20.2 / 20.2 us; 1, 2 or 8 pieces are within 5 % there.
+// Small calls, bound by latency, take one piece (the launch's comment).
+template <class V, class I, int N>
 __global__ __launch_bounds__(256) void permute_records_kernel(const V *__restrict__ src, V *__restrict__ dst,
                                                               const int32_t *__restrict__ perm, I n_rec, I words,
                                                               int to_layout) {
     const I n = n_rec * words;
-    const I t0 = (I)blockIdx.x * (256 * kPermutePieces) + threadIdx.x;
+    const I t0 = (I)blockIdx.x * (256 * N) + threadIdx.x;
     // every read is unconditional (of piece n - 1 or record 0 where there is
     // nothing to move), so that all of a work-item's reads are in flight at once
-    I rec[kPermutePieces], word[kPermutePieces];
-    int32_t p[kPermutePieces];
+    I rec[N], word[N];
+    int32_t p[N];
 #pragma unroll
-    for (int u = 0; u < kPermutePieces; ++u) {
+    for (int u = 0; u < N; ++u) {
         const I t = t0 + (I)(u * 256);
         const I c = t < n ? t : n - 1;
         rec[u] = c / words;
         word[u] = c - rec[u] * words;
         p[u] = perm[rec[u]];
     }
-    V v[kPermutePieces];
-    I to[kPermutePieces];
-    bool ok[kPermutePieces];
+    V v[N];
+    I to[N];
+    bool ok[N];
 #pragma unroll
-    for (int u = 0; u < kPermutePieces; ++u) {
+    for (int u = 0; u < N; ++u) {
         ok[u] = t0 + (I)(u * 256) < n && p[u] >= 0 && (I)p[u] < n_rec;
         const I o = (ok[u] ? (I)p[u] : (I)0) * words + word[u], i = rec[u] * words + word[u];
         to[u] = to_layout ? o : i;
         v[u] = src[to_layout ? i : o];
     }
 #pragma unroll
-    for (int u = 0; u < kPermutePieces; ++u)
+    for (int u = 0; u < N; ++u)
         if (ok[u]) dst[to[u]] = v[u];
 }
 

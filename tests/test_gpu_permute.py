@@ -40,3 +40,11 @@ def test_permute_matches_indexing(gpu_device, words, off_src, off_dst, n):
         got = out.cpu()
         assert torch.equal(got[off_dst:off_dst + n * words].view(n, words), ref)
         assert (got[:off_dst] == 7).all() and (got[off_dst + n * words:] == 7).all()
+
+
+# 12 pieces of 16, 9 of 8 and 5 of 4 bytes a record: the last call of one piece
+# per work-item (at most 524,288 pieces), the first of four, and one beyond
+@pytest.mark.parametrize("words,n", [(48, 43690), (48, 43691), (48, 60001), (18, 58254), (18, 58255), (5, 104857),
+                                     (5, 104858)])
+def test_permute_pieces_per_work_item(gpu_device, words, n):
+    test_permute_matches_indexing(gpu_device, words, 0, 0, n)
