@@ -106,6 +106,10 @@ dgc_status launch_batch(const dgc_batch::Header &h, const char *dev, int stage, 
 bool element_stage_ok(const dgc_dmesh *dm, int32_t precision) {
     const int most = dm->elem_type == DGC_TRI ? 6 : 4;
     if (!dm->elem_slots || dm->max_slots <= 0 || dm->max_slots > most) return false;
+    // f64: faster at every order, type and size measured, colored / element
+    // pass, us a step: 512 triangles p = 1 38 / 16, 996,972 triangles p = 2
+    // 1,072 / 714, 1,048,576 parallelograms p = 2 2,504 / 1,076, 1,572,864
+    // tetrahedra p = 1 2,161 / 1,669
     if (precision == DGC_F64) return true;
     // the f32 form keeps the rounding of the colored kernels, which the
     // element pass reproduces where those evaluate the volume term by teams
