@@ -227,3 +227,23 @@ def test_batch_with_refined_member(gpu_device, precision):
         b = _steps(D, U0, "default", precision)
         tol = 1e-14 * b.abs().max().item() if precision == "f64" else 1e-5 * (b - U0).abs().max().item()
         assert (U - b).abs().max().item() <= tol
+
+
+F32_CASES = ([(k, n, p) for k, n in (("periodic", 9), ("delaunay", 2000)) for p in range(4)]
+             + [(k, n, p) for k, n in (("quads", 10), ("quadbox", 17)) for p in range(4)]
+             + [(k, n, p) for k, n in (("hybrid", 16), ("hybridbox", 21)) for p in range(4)])
+
+
+@pytest.mark.parametrize("kind,size,p", F32_CASES)
+@pytest.mark.parametrize("layout", ["paper", "paired"])
+def test_f32_is_the_colored_step_bit_for_bit(gpu_device, kind, size, p, layout):
+    """Every element type and order whose f32 step takes the element pass
+    gives the bits of the launches that run without the element slots."""
+    import torch
+
+    D, _, _, Ug = _setup(kind, size, p, seed=4, layout=layout)
+    N, _, _, Un = _setup(kind, size, p, seed=4, layout=layout, with_slots=False)
+    assert torch.equal(Ug, Un)
+    a, b = _steps(D, Ug, "default", "f32"), _steps(N, Un, "default", "f32")
+    assert (a - Ug).abs().max().item() > 0
+    assert torch.equal(a, b)
