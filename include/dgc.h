@@ -338,6 +338,9 @@ typedef struct {
  * face slots per triangle; in f32 it is taken where it rounds exactly as the
  * colored launches do: conforming triangles at p <= 3 and parallelograms
  * colored with as many colors as an element has faces, and mixed meshes.
+ * It launches no face kernel, so surf_form, block_size and xcd_remap have no
+ * part in it (a surf_form that the type and order lack is refused all the
+ * same, DGC_E_UNSUPPORTED); they apply to the forms named explicitly.
  * Otherwise DGC_RK_DEFAULT is DGC_RK_FUSED_VOLUME for triangles at p <= 3, for
  * quadrilaterals (f32 only at p = 3) and for f64 tetrahedra at p = 1 when
  * vol_form is DGC_VOL_DEFAULT, and DGC_RK_FUSED otherwise (triangles at

@@ -222,7 +222,11 @@ class DeviceMesh:
         quadrature points one at a time "team_stream", lane = mode
         "mode_team" for tetrahedra at p = 1, or one work-item per face
         "thread"), the work-group size (0 = library default) and whether
-        work-groups are remapped to contiguous face ranges per XCD."""
+        work-groups are remapped to contiguous face ranges per XCD.  It
+        applies to ``surface_rhs`` and to the step forms that launch face
+        kernels; the one-pass step ("default" of ``set_rk_form`` where it
+        applies) launches none, and refuses a form that this mesh's type and
+        order lack as those do."""
         self.dm.surf_form = self.FORMS[form]
         self.dm.block_size = int(block)
         self.dm.xcd_remap = int(bool(xcd_remap))

@@ -122,6 +122,16 @@ dgc_status check_colors(const dgc_dmesh *dm) {
     return DGC_OK;
 }
 
+// An installed face form that no face kernel of this type and order has.  The
+// face launches refuse it themselves; the element stage runs none of them and
+// asks here.
+dgc_status check_surface_form(const dgc_dmesh *dm) {
+    if ((dm->surf_form == DGC_FORM_MODE_TEAM || dm->surf_form == DGC_FORM_PAIR_TEAM) &&
+        !(dm->elem_type == DGC_TET && dm->p == 1))
+        return fail(DGC_E_UNSUPPORTED, "mode and pair teams need N_p = 4 in 3D");
+    return DGC_OK;
+}
+
 template <int DIM, int NP, int Q, int QV, class T>
 struct Impl {
     static constexpr int REC = (DIM + 2) * NP;
@@ -538,7 +548,7 @@ dgc_status dgc_rk_step(const dgc_dmesh *dm, double *U, double dt, int32_t varian
         return fail(DGC_E_ARG, "dgc_dmesh: unknown rk_form");
     if (variant == DGC_SURF_COLORED && dm->rk_form == DGC_RK_DEFAULT && dm->vol_form == DGC_VOL_DEFAULT &&
         dgc::element_stage_ok(dm, precision)) {
-        if ((s = check_colors(dm)) != DGC_OK) return s;
+        if ((s = check_colors(dm)) != DGC_OK || (s = check_surface_form(dm)) != DGC_OK) return s;
         for (int stg = 0; stg < 3 && s == DGC_OK; ++stg)
             s = dgc::launch_element_stage(dm, ti, precision, stage_in[stg], stg == 0 ? nullptr : U, stage_out[stg],
                                           a[stg], b[stg], dt, st);

@@ -71,11 +71,12 @@ RK_FORMS = ("default", "fused_volume", "fused", "separate")
 
 
 def autotune_rk(dmesh, U, dt: float, precision: str = "f64", forms=RK_FORMS, reps: int = 5, warmup: int = 2):
-    """Pick the fastest SSP-RK3 step form of ``dmesh`` (with its installed face
-    launch) for a state shaped like ``U``; the steps run on a copy, ``U`` is
-    left unchanged.  Returns ``(best, [(form, ms), ...])`` and leaves ``best``
-    installed.  A form whose conditions do not hold on this mesh runs as the
-    next simpler one, so timing it is harmless."""
+    """Pick the fastest SSP-RK3 step form of ``dmesh`` for a state shaped like
+    ``U``; the steps run on a copy, ``U`` is left unchanged.  The forms that
+    launch face kernels run with the installed face launch; "default" runs
+    without one where it is the one-pass step.  Returns ``(best, [(form, ms),
+    ...])`` and leaves ``best`` installed.  A form whose conditions do not hold
+    on this mesh runs as the next simpler one, so timing it is harmless."""
     work = U.clone()
     ws = dmesh.workspace("rk", "colored", precision)
     results = []

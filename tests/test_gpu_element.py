@@ -247,3 +247,23 @@ def test_f32_is_the_colored_step_bit_for_bit(gpu_device, kind, size, p, layout):
     a, b = _steps(D, Ug, "default", "f32"), _steps(N, Un, "default", "f32")
     assert (a - Ug).abs().max().item() > 0
     assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("kind,size,p", [("periodic", 6, 2), ("quads", 6, 1), ("hybrid", 8, 1), ("tets", 3, 0),
+                                         ("tets", 3, 2)])
+@pytest.mark.parametrize("form", ["mode_team", "pair_team"])
+def test_face_form_that_the_mesh_lacks_is_refused(gpu_device, kind, size, p, form):
+    """The element pass launches no face kernel, but refuses an installed face
+    form as the colored launches do; a form that exists is accepted."""
+    D, _, _, Ug = _setup(kind, size, p)
+    D.set_launch(form)
+    for f in ("default", "separate"):
+        with pytest.raises(dgc.DgcError) as e:
+            _steps(D, Ug, f, n=1)
+        assert e.value.code == -6, f   # DGC_E_UNSUPPORTED
+    D.set_launch("team", 64, True)
+    D.set_rk_form("default")
+    _steps(D, Ug, "default", n=1)
+    T, _, _, Ut = _setup("tets", 3, 1)
+    T.set_launch(form)
+    _steps(T, Ut, "default", n=1)
