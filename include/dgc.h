@@ -529,13 +529,16 @@ dgc_status dgc_volume_rhs_batched(const void *host_desc, const void *dev_desc, i
 /* One SSP-RK3 step of every mesh of the batch with its own dt: a fixed
  * sequence of launches (plus one for the f32 shadow), independent of the
  * number of meshes, so it can be captured once in a graph and replayed.
- * When every member can run the one-pass element stage (see DGC_RK_DEFAULT)
- * a step is three launches.  Otherwise, when every member has exactly one face of each color (conforming meshes
- * colored with as many colors as an element has faces), each stage is one
- * launch per color, the first also evaluating the volume term where the
- * single-mesh DGC_RK_DEFAULT step does (triangles p <= 3, quadrilaterals,
- * f64 tetrahedra at p = 1) and, in f64, the last writing the stage
- * combination; otherwise 3 x (volume + one launch per color + combine). */
+ * When every member has the default rk_form and vol_form and can run the
+ * one-pass element stage (see DGC_RK_DEFAULT), a step is three launches.
+ * Otherwise (an explicit form of any member, whichever it is, asks for the
+ * colored launches), when every member has exactly one face of each color
+ * (conforming meshes colored with as many colors as an element has faces),
+ * each stage is one launch per color, the first also evaluating the volume
+ * term where the single-mesh DGC_RK_DEFAULT step does (triangles p <= 3,
+ * quadrilaterals, f64 tetrahedra at p = 1) and, in f64, the last writing the
+ * stage combination; otherwise 3 x (volume + one launch per color +
+ * combine). */
 dgc_status dgc_rk_step_batched(const void *host_desc, const void *dev_desc, void *stream);
 
 /* Library build identification (static string). */

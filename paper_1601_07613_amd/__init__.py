@@ -206,7 +206,9 @@ class DeviceMesh:
         conforming triangles at p <= 3, parallelograms and mixed meshes), and
         otherwise is "fused_volume" for triangles at p <= 3, quadrilaterals
         (f32 only at p = 3) and f64 tetrahedra at p = 1, else "fused"
-        (tetrahedra at p = 2: "separate")."""
+        (tetrahedra at p = 2: "separate").  A ``Batch`` reads the forms of its
+        members when it is made: one explicit form among them, and it steps
+        with the colored launches."""
         self.dm.rk_form = self.RK_FORMS[form]
 
     def set_volume_form(self, form: str = "default") -> None:

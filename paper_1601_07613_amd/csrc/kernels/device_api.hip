@@ -132,6 +132,12 @@ dgc_status check_surface_form(const dgc_dmesh *dm) {
     return DGC_OK;
 }
 
+// whether DGC_RK_DEFAULT runs this mesh's stages as one pass over the elements;
+// an explicit step or volume form asks for the colored launches
+bool takes_element_stage(const dgc_dmesh *dm, int32_t precision) {
+    return dm->rk_form == DGC_RK_DEFAULT && dm->vol_form == DGC_VOL_DEFAULT && dgc::element_stage_ok(dm, precision);
+}
+
 template <int DIM, int NP, int Q, int QV, class T>
 struct Impl {
     static constexpr int REC = (DIM + 2) * NP;
@@ -546,8 +552,7 @@ dgc_status dgc_rk_step(const dgc_dmesh *dm, double *U, double dt, int32_t varian
     double *stage_out[3] = {U1, U2, U};
     if (dm->rk_form < DGC_RK_DEFAULT || dm->rk_form > DGC_RK_FUSED_VOLUME)
         return fail(DGC_E_ARG, "dgc_dmesh: unknown rk_form");
-    if (variant == DGC_SURF_COLORED && dm->rk_form == DGC_RK_DEFAULT && dm->vol_form == DGC_VOL_DEFAULT &&
-        dgc::element_stage_ok(dm, precision)) {
+    if (variant == DGC_SURF_COLORED && takes_element_stage(dm, precision)) {
         if ((s = check_colors(dm)) != DGC_OK || (s = check_surface_form(dm)) != DGC_OK) return s;
         for (int stg = 0; stg < 3 && s == DGC_OK; ++stg)
             s = dgc::launch_element_stage(dm, ti, precision, stage_in[stg], stg == 0 ? nullptr : U, stage_out[stg],
@@ -892,7 +897,7 @@ dgc_status dgc_batch_describe(int32_t n_mesh, const dgc_dmesh *meshes, double *c
         nb_elem += (d.n_elem * vteam + kBlock - 1) / kBlock;
         nb_dof += (d.n_elem * d.n_var * d.n_p + kBlock - 1) / kBlock;
         nb_stage += (d.n_elem + epb - 1) / epb;
-        elem_slots = dgc::element_stage_ok(&d, precision) ? std::max(elem_slots, d.max_slots) : INT32_MAX;
+        elem_slots = takes_element_stage(&d, precision) ? std::max(elem_slots, d.max_slots) : INT32_MAX;
     }
     if (elem_slots == INT32_MAX) elem_slots = nb_stage = 0;
     for (int c = 0; c < nc; ++c)

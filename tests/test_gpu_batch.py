@@ -161,3 +161,75 @@ def test_graph_replays_match_eager():
         for (_, Ug, _, _), (_, Ue, _, _) in zip(g_members, e_members):
             assert torch.equal(Ug, Ue), rep
         del junk
+
+
+# -- the colored launches of a batch: members without element slots, or with an
+# explicit step form ---------------------------------------------------------
+FAMILIES = {"tri": TRI[:3], "quad": QUAD, "tet": TET}
+
+
+def _colored_batch(family, p, precision, how):
+    """Members whose batch runs the colored launches, fresh states included."""
+    import paper_1601_07613_amd as dgc
+
+    members = [_member(k, s, sd, p, precision, smooth=True) for k, s, sd in FAMILIES[family]]
+    if how == "no_slots":
+        members = [(dgc.DeviceMesh(D.mesh, p, with_slots=False), U, ws, dt) for D, U, ws, dt in members]
+    elif how == "one_rk_form":
+        members[1][0].set_rk_form("fused")
+    elif how == "volume_form":
+        for D, _, _, _ in members:
+            D.set_volume_form("team")
+    return members
+
+
+@pytest.mark.parametrize("family,p", [("tri", 0), ("tri", 1), ("tri", 2), ("tri", 3), ("tri", 4), ("quad", 1),
+                                      ("quad", 2), ("quad", 3), ("tet", 0), ("tet", 1), ("tet", 2)])
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+def test_batched_colored_launches_match_separate(precision, family, p):
+    """The batch's colored launches (the volume term in the first color's, the
+    combination in the last color's where the header says so) against the
+    single mesh's separate kernels: 1e-14 of the state in f64, 1e-5 of the
+    change in f32."""
+    import torch
+
+    import paper_1601_07613_amd as dgc
+
+    members = _colored_batch(family, p, precision, "no_slots")
+    start = [U.clone() for _, U, _, _ in members]
+    B = dgc.Batch(members, precision=precision)
+    for _ in range(3):
+        B.rk_step()
+    for (D, U, _, dt), U0 in zip(members, start):
+        R = U0.clone()
+        ws = D.workspace("rk", "colored", precision)
+        D.set_rk_form("separate")
+        for _ in range(3):
+            D.rk_step(R, dt, precision=precision, ws=ws)
+        torch.cuda.synchronize()
+        change = (R - U0).abs().max().item()
+        assert change > 0
+        tol = 1e-14 * R.abs().max().item() if precision == "f64" else 1e-5 * change
+        assert (U - R).abs().max().item() <= tol
+
+
+@pytest.mark.parametrize("family,p", [("tri", 2), ("quad", 2), ("tet", 1)])
+@pytest.mark.parametrize("how", ["one_rk_form", "volume_form"])
+def test_batch_heeds_its_members_forms(family, p, how):
+    """An explicit step or volume form among the members selects the colored
+    launches: the bits of the batch without element slots, which in f64 are
+    not those of the element pass."""
+    import torch
+
+    import paper_1601_07613_amd as dgc
+
+    out = {}
+    for h in (how, "no_slots", "default"):
+        members = _colored_batch(family, p, "f64", h)
+        B = dgc.Batch(members)
+        for _ in range(3):
+            B.rk_step()
+        torch.cuda.synchronize()
+        out[h] = [U for _, U, _, _ in members]
+    assert all(torch.equal(a, b) for a, b in zip(out[how], out["no_slots"]))
+    assert not all(torch.equal(a, b) for a, b in zip(out["default"], out["no_slots"]))

@@ -267,3 +267,28 @@ def test_face_form_that_the_mesh_lacks_is_refused(gpu_device, kind, size, p, for
     T, _, _, Ut = _setup("tets", 3, 1)
     T.set_launch(form)
     _steps(T, Ut, "default", n=1)
+
+
+# the schedule that the default step without element slots stands for
+NO_SLOTS = ([("periodic", 9, p, "f64", "fused_volume" if p <= 3 else "fused") for p in range(6)]
+            + [("delaunay", 900, p, "f32", "fused_volume" if p <= 3 else "fused") for p in range(6)]
+            + [("quadbox", 9, p, "f64", "fused_volume" if p <= 2 else "fused") for p in range(4)]
+            + [("quads", 8, p, "f32", "fused_volume") for p in range(4)]
+            + [("tets", 3, p, "f64", ("fused", "fused_volume", "separate")[p]) for p in range(3)]
+            + [("tetbox", 3, p, "f32", "separate") for p in range(3)])
+
+
+@pytest.mark.parametrize("kind,size,p,precision,form", NO_SLOTS)
+def test_default_without_slots(gpu_device, kind, size, p, precision, form):
+    """Without the element -> face slots the default step is the documented
+    colored schedule, bit for bit, and agrees with the separate launches."""
+    import torch
+
+    N, _, _, Un = _setup(kind, size, p, seed=6, with_slots=False)
+    a, b = _steps(N, Un, "default", precision), _steps(N, Un, form, precision)
+    assert torch.equal(a, b)
+    c = _steps(N, Un, "separate", precision)
+    change = (c - Un).abs().max().item()
+    assert change > 0
+    tol = 1e-14 * c.abs().max().item() if precision == "f64" else 1e-5 * change
+    assert (a - c).abs().max().item() <= tol
