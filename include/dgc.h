@@ -531,6 +531,9 @@ dgc_status dgc_volume_rhs_batched(const void *host_desc, const void *dev_desc, i
  * number of meshes, so it can be captured once in a graph and replayed.
  * When every member has the default rk_form and vol_form and can run the
  * one-pass element stage (see DGC_RK_DEFAULT), a step is three launches.
+ * A member's result is bit for bit what it is beside other members of its kind
+ * (conforming, refined); where the kinds are mixed it may differ from that by
+ * rounding, because the batch launches what all of its members can run.
  * Otherwise (an explicit form of any member, whichever it is, asks for the
  * colored launches), when every member has exactly one face of each color
  * (conforming meshes colored with as many colors as an element has faces),

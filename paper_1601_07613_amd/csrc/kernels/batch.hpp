@@ -4,8 +4,12 @@
 // uniform load), then does exactly the per-face / per-element / per-DOF work
 // of the single-mesh kernels on that mesh's arrays.  Meshes are disjoint, so
 // one launch per color stays race-free (Algorithm 1 applied to the union of
-// the meshes), and a mesh's results do not depend on the other members of
-// the batch.
+// the meshes).  A mesh's volume and surface terms do not depend on the other
+// members of the batch, and neither does its step among members of its own
+// kind; the last bits of the step change where conforming and refined meshes
+// are mixed, since the batch then launches what all of them can run: the
+// separate kernels in place of the fused first and last colors, or the
+// six-slot element pass, which sums an element's sides in another order.
 #pragma once
 
 #include <hip/hip_runtime.h>
