@@ -78,6 +78,13 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_wave_barrier();
 }
 
+// The shapes whose f32 pass rounds as the colored step does, where the colored
+// volume term is summed by teams: mixed meshes, parallelograms, and conforming
+// triangles at p <= 3.  The others have no f32 kernel.
+constexpr bool f32_element_shape(int dim, int n_p, int face_slots, bool mixed) {
+    return dim == 2 && (mixed || face_slots == 4 || (face_slots == 3 && n_p <= 10));
+}
+
 // Launch shape and LDS sizes, shared by host and device.
 template <int DIM, int NP, int Q, int QV, int FS, bool MIXED, class T>
 struct ElemCfg {
@@ -95,6 +102,7 @@ struct ElemCfg {
     // local faces, so that its own tables are the same for every lane and
     // come through the scalar cache (FACES)
     static constexpr bool PROJ = sizeof(T) == 4;
+    static_assert(!PROJ || f32_element_shape(DIM, NP, FS, MIXED), "no f32 pass for this shape");
     static constexpr bool FACES = !PROJ && !MIXED && FS == NF && (DIM == 2 || Q == 3);
     // The wave's region: planes of one variable's traces at the group's
     // points, own then neighbour's, then planes of the side geometry.  Odd
@@ -111,7 +119,7 @@ struct ElemCfg {
     // 128 and four with two (991,232 triangles at p = 2: 226 against 219 us a
     // stage; 589,824 parallelograms at p = 2 234 with four sides, 217 with
     // one, before the late x read below).
-    static constexpr int FG = PROJ ? (NP >= 9 || FS > 4 ? 1 : FS)
+    static constexpr int FG = PROJ ? (NP >= 9 ? 1 : FS)
                               : NP == 3 && FS == 3 ? 3
                               : Q == 2 || (NP == 6 && FS == 3) ? 2 : 1;
     // Refined meshes: only elements beside smaller ones fill more than three
@@ -143,7 +151,7 @@ struct ElemCfg {
     __host__ __device__ static constexpr int tab_len(int n_codes) {
         return PROJ ? 2 * n_codes * Q * NP : n_codes * Q * NP + Q;
     }
-    static constexpr bool VFUSED = PROJ && M == 4 && !MIXED && FS <= 4;
+    static constexpr bool VFUSED = PROJ && !MIXED;
     static constexpr int VTAB = MIXED ? 2 * (1 + DIM) * QV * NP : 0;  // mixed meshes: both kinds' volume tables
 
     __host__ __device__ static constexpr size_t lds_bytes(int n_codes) {

@@ -73,16 +73,25 @@ dgc_status launched(const char *what) {
 template <class S, class T>
 using Cfg = dgc_dev::ElemCfg<S::kDim, S::kNp, S::kQ, S::kQv, S::kFs, S::kMixed, T>;
 
+template <class S, class T>
+constexpr bool built() {
+    return sizeof(T) == 8 || dgc_dev::f32_element_shape(S::kDim, S::kNp, S::kFs, S::kMixed);
+}
+
 template <class T>
 dgc_status launch(const dgc_dmesh *dm, const dgc_dev::ElemStageArgs &A, const dgc_dev::ElemTables &tab,
                   hipStream_t st) {
     return dispatch(dm->elem_type, dm->p, dm->max_slots, [&](auto shape) {
         using S = decltype(shape);
-        using C = Cfg<S, T>;
-        hipLaunchKernelGGL((dgc_dev::element_stage_kernel<S::kDim, S::kNp, S::kQ, S::kQv, S::kFs, S::kMixed, T>),
-                           dim3((unsigned)((A.n_elem + C::EPB - 1) / C::EPB)), dim3(C::BLOCK),
-                           C::lds_bytes(tab.n_codes), st, A, tab, dm->max_slots);
-        return launched("element stage launch");
+        if constexpr (!built<S, T>()) {
+            return fail(DGC_E_UNSUPPORTED, "no f32 element stage built for this element type and order");
+        } else {
+            using C = Cfg<S, T>;
+            hipLaunchKernelGGL((dgc_dev::element_stage_kernel<S::kDim, S::kNp, S::kQ, S::kQv, S::kFs, S::kMixed, T>),
+                               dim3((unsigned)((A.n_elem + C::EPB - 1) / C::EPB)), dim3(C::BLOCK),
+                               C::lds_bytes(tab.n_codes), st, A, tab, dm->max_slots);
+            return launched("element stage launch");
+        }
     });
 }
 
@@ -92,6 +101,8 @@ dgc_status launch_batch(const dgc_batch::Header &h, const char *dev, int stage, 
         using S = decltype(shape);
         if constexpr (S::kMixed) {
             return fail(DGC_E_UNSUPPORTED, "mixed meshes are not batched");
+        } else if constexpr (!built<S, T>()) {
+            return fail(DGC_E_UNSUPPORTED, "no f32 element stage built for this element type and order");
         } else {
             using C = Cfg<S, T>;
             hipLaunchKernelGGL((dgc_dev::batch_element_stage_kernel<S::kDim, S::kNp, S::kQ, S::kQv, S::kFs, false, T>),
@@ -111,11 +122,13 @@ bool element_stage_ok(const dgc_dmesh *dm, int32_t precision) {
     // 1,072 / 714, 1,048,576 parallelograms p = 2 2,504 / 1,076, 1,572,864
     // tetrahedra p = 1 2,161 / 1,669
     if (precision == DGC_F64) return true;
-    // the f32 form keeps the rounding of the colored kernels, which the
-    // element pass reproduces where those evaluate the volume term by teams
-    if (dm->elem_type == DGC_MIXED) return true;
-    if (dm->elem_type == DGC_TET || dm->n_colors != dm->max_slots) return false;
-    return dm->elem_type == DGC_QUAD || (dm->p <= 3 && dm->max_slots == 3);
+    // the f32 form keeps the rounding of the colored kernels (slot order =
+    // color order); uniform meshes also need a face of each color per element,
+    // as the colored step that carries the volume term does
+    const bool mixed = dm->elem_type == DGC_MIXED;
+    const int faces = dm->elem_type == DGC_TRI ? 3 : 4;
+    return (mixed || (dm->max_slots == faces && dm->n_colors == faces)) &&
+           dgc_dev::f32_element_shape(dm->elem_type == DGC_TET ? 3 : 2, dm->n_p, faces, mixed);
 }
 
 dgc_status launch_element_stage(const dgc_dmesh *dm, const dgc_table_info &ti, int32_t precision, const double *y,
