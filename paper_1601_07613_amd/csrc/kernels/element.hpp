@@ -100,10 +100,12 @@ struct ElemCfg {
     // the colored kernels round; f64 on conforming meshes whose face rule
     // looks the same from both sides: the sides in the order of the element's
     // local faces, so that its own tables are the same for every lane and
-    // come through the scalar cache (FACES)
+    // come through the scalar cache (FACES).  Not at p = 0, whose tables are
+    // constants: in slot order, the color order, a wave's sides lie next to each
+    // other in the face arrays, which is most of what that pass reads.
     static constexpr bool PROJ = sizeof(T) == 4;
     static_assert(!PROJ || f32_element_shape(DIM, NP, FS, MIXED), "no f32 pass for this shape");
-    static constexpr bool FACES = !PROJ && !MIXED && FS == NF && (DIM == 2 || Q == 3);
+    static constexpr bool FACES = !PROJ && !MIXED && NP > 1 && FS == NF && (DIM == 2 || Q == 3);
     // The wave's region: planes of one variable's traces at the group's
     // points, own then neighbour's, then planes of the side geometry.  Odd
     // plane lengths spread a store of the M variables over the banks.
@@ -118,8 +120,14 @@ struct ElemCfg {
     // and less LDS: 131 registers and three waves per SIMD with three sides,
     // 128 and four with two (991,232 triangles at p = 2: 226 against 219 us a
     // stage; 589,824 parallelograms at p = 2 234 with four sides, 217 with
-    // one, before the late x read below).
+    // one, before the late x read below).  2D at p = 0: all sides, three of a
+    // refined triangle, whose reads are then in flight together (one at a time
+    // and in face order, as it was at first: 980,000 triangles 286 against 173
+    // us a step, the colored launches 219; 589,824 parallelograms 225, 128 and
+    // 189; 944,292 triangles of a refined mesh 295 and 235; 512 triangles 17.3
+    // and 12.4.  Tetrahedra at p = 0 are slower with all sides, 368 against 316)
     static constexpr int FG = PROJ ? (NP >= 9 ? 1 : FS)
+                              : NP == 1 && DIM == 2 ? (FS > 4 ? 3 : FS)
                               : NP == 3 && FS == 3 ? 3
                               : Q == 2 || (NP == 6 && FS == 3) ? 2 : 1;
     // Refined meshes: only elements beside smaller ones fill more than three
