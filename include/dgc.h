@@ -306,7 +306,10 @@ typedef struct {
                                   each XCD one contiguous range of faces (shared L2 lines) */
     int32_t vol_form;          /* DGC_VOL_* */
     int32_t rk_form;           /* DGC_RK_* */
-    int32_t pad_;
+    int32_t far_percent;       /* 0 (not known) to 100: share of the elements whose neighbour across a
+                                  slot lies more than 4,096 elements from the neighbour that the
+                                  element before it has there, on conforming 2D meshes.  Large
+                                  where the numbering has no order (DGC_RK_DEFAULT at p <= 1) */
     const int8_t *elem_kind;   /* [n_elem] DGC_ARR_DEV_ELEM_KIND (mixed meshes; NULL otherwise) */
 } dgc_dmesh;
 
@@ -338,6 +341,8 @@ typedef struct {
  * face slots per triangle; in f32 it is taken where it rounds exactly as the
  * colored launches do: conforming triangles at p <= 3 and parallelograms
  * colored with as many colors as an element has faces, and mixed meshes.
+ * It gathers an element's face and neighbour data, so large meshes at p = 0
+ * and 1 whose numbering has no order (far_percent) keep the colored launches.
  * It launches no face kernel, so surf_form, block_size and xcd_remap have no
  * part in it (a surf_form that the type and order lack is refused all the
  * same, DGC_E_UNSUPPORTED); they apply to the forms named explicitly.

@@ -128,6 +128,22 @@ def _stream_ptr(stream=None):
     return C.c_void_p(s.cuda_stream)
 
 
+def _far_percent(mesh: Mesh, info: dict, slots: np.ndarray) -> int:
+    """``dgc_dmesh.far_percent`` of a conforming 2D mesh (0 below the sizes
+    that it matters for): how often the neighbours of consecutive elements lie
+    more than 4,096 elements apart.  Ordered numberings and the paired layout
+    2-54, a random numbering 65-73 in the paper's layout and 97-98 in none."""
+    if info["dim"] != 2 or info["max_level"] > 0 or info["n_face"] < 250_000:
+        return 0
+    lr = mesh.export("dev_face_lr").reshape(2, -1)
+    s = slots.reshape(info["max_slots"], -1)
+    f = np.maximum(s, 0) >> 1
+    nb = np.where(s & 1, lr[0][f], lr[1][f])
+    both = (s[:, 1:] >= 0) & (s[:, :-1] >= 0)
+    far = np.abs(np.diff(nb, axis=1)) > 4096
+    return int(round(100.0 * np.count_nonzero(far & both) / max(np.count_nonzero(both), 1)))
+
+
 class DeviceMesh:
     """Device-resident arrays of one laid-out mesh at order ``p`` (torch tensors)."""
 
@@ -156,7 +172,8 @@ class DeviceMesh:
         self.face_code = up(mesh.export("dev_face_code"))
         self.face_geo = up(mesh.export("dev_face_geo"))
         self.elem_geo = up(mesh.export("dev_elem_geo"))
-        self.elem_slots = up(mesh.export("dev_elem_slots")) if with_slots else None
+        slots = mesh.export("dev_elem_slots") if with_slots else None
+        self.elem_slots = up(slots) if with_slots else None
         self.tables = up(tab)
         self.elem_kind = up(mesh.export("dev_elem_kind")) if info["elem_type"] == DGC_MIXED else None
         self.elem_new = mesh.export("elem_new").astype(np.int64)
@@ -186,6 +203,7 @@ class DeviceMesh:
         dm.xcd_remap = 0
         dm.vol_form = 0
         dm.rk_form = 0
+        dm.far_percent = _far_percent(mesh, info, slots) if with_slots and p <= 1 else 0
         dm.elem_kind = self.elem_kind.data_ptr() if self.elem_kind is not None else None
         self.dm = dm
 

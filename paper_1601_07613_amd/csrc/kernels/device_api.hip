@@ -552,7 +552,7 @@ dgc_status dgc_rk_step(const dgc_dmesh *dm, double *U, double dt, int32_t varian
     double *stage_out[3] = {U1, U2, U};
     if (dm->rk_form < DGC_RK_DEFAULT || dm->rk_form > DGC_RK_FUSED_VOLUME)
         return fail(DGC_E_ARG, "dgc_dmesh: unknown rk_form");
-    if (variant == DGC_SURF_COLORED && takes_element_stage(dm, precision)) {
+    if (variant == DGC_SURF_COLORED && takes_element_stage(dm, precision) && !dgc::element_stage_scattered(dm)) {
         if ((s = check_colors(dm)) != DGC_OK || (s = check_surface_form(dm)) != DGC_OK) return s;
         for (int stg = 0; stg < 3 && s == DGC_OK; ++stg)
             s = dgc::launch_element_stage(dm, ti, precision, stage_in[stg], stg == 0 ? nullptr : U, stage_out[stg],

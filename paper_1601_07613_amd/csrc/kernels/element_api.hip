@@ -131,6 +131,30 @@ bool element_stage_ok(const dgc_dmesh *dm, int32_t precision) {
            dgc_dev::f32_element_shape(dm->elem_type == DGC_TET ? 3 : 2, dm->n_p, faces, mixed);
 }
 
+bool element_stage_scattered(const dgc_dmesh *dm) {
+    // Where the numbering has no order, every face value, code and neighbour id
+    // that an element gathers is a line of its own, about eight a side; a
+    // colored launch reads them in face order.  That outweighs the right-hand
+    // side's traffic for the shortest records, once the arrays leave the
+    // caches.  us a step, colored / element pass, f64, random numbering:
+    //   p = 0, the paper's layout (far_percent 64-74): 389k faces of triangles
+    //     108 / 110, 480k 124 / 139, 1.47M 318 / 503; 442k of parallelograms
+    //     134 / 134, 520k 149 / 164; 594k of a mixed mesh 205 / 195 (f32 184 /
+    //     193), 791k 248 / 267; no renumbering (96-99): 389k 129 / 147
+    //   p = 1, no renumbering: 480k faces of triangles 242 / 248 (f32 254 /
+    //     241), 608k 305 / 319 (309 / 314), 1.47M 752 / 835; 720k of
+    //     parallelograms 327 / 351
+    //   p = 1, the paper's layout: 1.47M of triangles 656 / 648; 720k of
+    //     parallelograms 299 / 311 (f32 300 / 297), 1.18M 504 / 531, 2M 856 / 935
+    // Mixed meshes at p = 1, p >= 2 and tetrahedra are faster in one pass.
+    const int64_t E = dm->n_face;
+    const int far = dm->far_percent;
+    if (dm->elem_type == DGC_TET) return false;
+    if (dm->p == 0) return far >= 60 && E >= (dm->elem_type == DGC_MIXED ? 700000 : 450000);
+    if (dm->p != 1 || dm->elem_type == DGC_MIXED) return false;
+    return (far >= 85 && E >= 600000) || (dm->elem_type == DGC_QUAD && far >= 60 && E >= 1100000);
+}
+
 dgc_status launch_element_stage(const dgc_dmesh *dm, const dgc_table_info &ti, int32_t precision, const double *y,
                                 const double *x, double *out, double a, double b, double dt, hipStream_t st) {
     const dgc_dev::ElemStageArgs A{dm->elem_slots, dm->face_lr, dm->face_code, dm->face_geo, dm->elem_geo,

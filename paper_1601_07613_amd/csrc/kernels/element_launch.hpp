@@ -14,6 +14,9 @@ namespace dgc {
 // whose colored step it reproduces in rounding
 bool element_stage_ok(const dgc_dmesh *dm, int32_t precision);
 
+// whether a mesh is too scattered for the element pass to be the faster one
+bool element_stage_scattered(const dgc_dmesh *dm);
+
 // one SSP-RK3 stage out = a x + b (y + dt rhs(y)) (x null: x = y, with a = 0)
 dgc_status launch_element_stage(const dgc_dmesh *dm, const dgc_table_info &ti, int32_t precision, const double *y,
                                 const double *x, double *out, double a, double b, double dt, hipStream_t st);

@@ -292,3 +292,27 @@ def test_default_without_slots(gpu_device, kind, size, p, precision, form):
     assert change > 0
     tol = 1e-14 * c.abs().max().item() if precision == "f64" else 1e-5 * change
     assert (a - c).abs().max().item() <= tol
+
+
+def test_scattered_numbering_keeps_the_colored_step(gpu_device):
+    """p = 0 on a large mesh in a random numbering: the colored launches; the
+    same mesh in an ordered one, or said to be, the element pass."""
+    import torch
+
+    m = synth.periodic_tri(390, seed=1)          # 456,300 faces
+    for scattered in (False, True):
+        mm = synth.shuffle_elements(m, 3) if scattered else m
+        M = dgc.Mesh.build(mm["elem_vert"], mm["elem_xyz"])
+        M.color(seed=1, layout="paper")
+        D = dgc.DeviceMesh(M, 0)
+        assert (D.dm.far_percent >= 60) == scattered
+        cen = synth.element_centroid(mm["elem_xyz"])
+        U0 = synth.perturbed_dofs(synth.element_measure(mm["elem_xyz"]),
+                                  synth.density_wave_states(cen, vel=(0.5, 0.3)), 1, seed=2)
+        Ug = torch.from_numpy(D.to_layout(U0)).cuda()
+        a, b = _steps(D, Ug, "default"), _steps(D, Ug, "fused_volume")
+        D.dm.far_percent = 0
+        c = _steps(D, Ug, "default")
+        assert torch.equal(a, b) == scattered
+        assert torch.equal(a, c) != scattered
+        assert (c - b).abs().max().item() <= 1e-14 * b.abs().max().item()

@@ -264,3 +264,21 @@ def test_surface_entry_rejects_missing_workspace_without_launching():
     assert L.dgc_surface_rhs(C.byref(dm), 0x1000, 0x1000, 0, 0, None, 0, None) == -3  # no colors
     dm.p = 7
     assert L.dgc_surface_rhs(C.byref(dm), 0x1000, 0x1000, 1, 0, None, 0, None) == -6  # unsupported order
+
+
+def test_far_percent_tells_random_numberings():
+    """``dgc_dmesh.far_percent``: below 55 for ordered numberings and layouts
+    that order, 60 and more for random ones; 0 where the step does not ask."""
+    import synth
+
+    dgc = pytest.importorskip("paper_1601_07613_amd")
+    for make, n in ((synth.periodic_tri, 300), (synth.quad_grid, 360)):
+        m = make(n, seed=1)
+        for layout, shuffle, low, high in (("paired", True, 0, 55), ("paper_sfc", True, 0, 55), ("paper", False, 0, 55),
+                                           ("paper", True, 60, 84), ("none", True, 85, 100)):
+            mm = synth.shuffle_elements(m, 3) if shuffle else m
+            M = dgc.Mesh.build(mm["elem_vert"], mm["elem_xyz"])
+            M.color(seed=1, layout=layout)
+            far = dgc.DeviceMesh(M, 0, device="cpu").dm.far_percent
+            assert low <= far <= high, (n, layout, shuffle, far)
+            assert dgc.DeviceMesh(M, 2, device="cpu").dm.far_percent == 0
