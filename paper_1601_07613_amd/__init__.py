@@ -471,15 +471,26 @@ class Batch:
 
     def capture(self, steps: int = 1, warm: bool = True):
         """Capture ``steps`` batched RK3 steps in a graph; returns the graph
-        (replay with ``.replay()``).  ``warm`` first runs a stage-0 volume +
-        surface evaluation, which loads the kernels before the capture (it
-        writes only the stage right-hand side in the workspaces, never a
-        state); a caller that has already stepped this batch may skip it."""
+        (replay with ``.replay()``), which reads this batch's descriptor and
+        its members' buffers: they have to outlive it.  ``warm`` first runs a stage-0 volume +
+        surface evaluation (it writes only the stage right-hand side in the
+        workspaces, never a state) and a default step of a copy of the smallest
+        member, which load the colored step's kernels and the one-pass step's
+        before the capture; a caller that has already stepped this batch may
+        skip it."""
         import torch
 
         if warm:
             self.volume(0)
             self.surface(0)
+            i = min(range(len(self.members)), key=lambda j: self.members[j][1].numel())
+            _, U, ws, dt = self.members[i]
+            dm = _lib.DMesh.from_buffer_copy(self._dms[i])
+            dm.surf_form = dm.block_size = dm.xcd_remap = dm.vol_form = dm.rk_form = dm.far_percent = 0
+            Uc, wc = U.clone(), torch.empty_like(ws)
+            _lib.check(_L.dgc_rk_step(C.byref(dm), Uc.data_ptr(), float(dt), VARIANTS["colored"],
+                                      PRECISIONS[self.precision], wc.data_ptr(), wc.numel(), _stream_ptr()),
+                       "dgc_rk_step")
         torch.cuda.synchronize()
         g = torch.cuda.CUDAGraph()
         with torch.cuda.graph(g):

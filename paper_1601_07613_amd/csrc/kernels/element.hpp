@@ -312,7 +312,8 @@ __device__ __forceinline__ void element_stage(const ElemStageArgs &A, const Elem
 
 #pragma unroll
     for (int i = 0; i < FS; ++i) {
-        // a malformed face (ids or codes out of range) is skipped, never dereferenced
+        // a side whose slot, neighbour or codes are out of range is skipped,
+        // never dereferenced
         ok[i] = lane_ok & ((uint32_t)slot[i] < E2) & (nb[i] < K) & (co[i] < nc) & (cn[i] < nc) &
                 ((nb[i] >= 0) | !(slot[i] & 1));
         nb[i] = ok[i] ? nb[i] : -1;

@@ -233,3 +233,70 @@ def test_batch_heeds_its_members_forms(family, p, how):
         out[h] = [U for _, U, _, _ in members]
     assert all(torch.equal(a, b) for a, b in zip(out[how], out["no_slots"]))
     assert not all(torch.equal(a, b) for a, b in zip(out["default"], out["no_slots"]))
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+def test_capture_loads_the_steps_kernels_first(monkeypatch, precision):
+    """``capture(warm=True)`` steps a copy of the smallest member before the
+    capture begins, whatever face form is installed, and leaves every state."""
+    import torch
+
+    import paper_1601_07613_amd as dgc
+
+    members = [_member(k, s, sd, 1, precision, smooth=True) for k, s, sd in TRI[:3]]
+    members[2][0].set_launch("mode_team")       # the batch does not launch it
+    U0 = [U.clone() for _, U, _, _ in members]
+    calls = []
+    step = dgc._L.dgc_rk_step
+
+    def recorded(dm, U, *a):
+        calls.append((torch.cuda.is_current_stream_capturing(), U))
+        return step(dm, U, *a)
+
+    monkeypatch.setattr(dgc._L, "dgc_rk_step", recorded)
+    B = dgc.Batch(members, precision=precision)
+    g = B.capture()
+    torch.cuda.synchronize()
+    assert [c for c, _ in calls] == [False]
+    assert calls[0][1] not in [U.data_ptr() for _, U, _, _ in members]
+    assert all(torch.equal(U, V) for (_, U, _, _), V in zip(members, U0))
+    E = dgc.Batch([(D, V, D.workspace("rk", "colored", precision), dt) for (D, _, _, dt), V in zip(members, U0)],
+                  precision=precision)
+    for _ in range(3):
+        g.replay()
+        E.rk_step()
+        torch.cuda.synchronize()
+        assert all(torch.equal(U, V) for (_, U, _, _), V in zip(members, U0))
+
+
+CAPTURE_FIRST = """
+import sys
+import torch
+sys.path.insert(0, sys.argv[1])
+from tests.test_gpu_batch import _member
+import paper_1601_07613_amd as dgc
+members = [_member("periodic", n, n, 2, sys.argv[2], smooth=True) for n in (12, 7)]
+copies = [(D, U.clone(), D.workspace("rk", "colored", sys.argv[2]), dt) for D, U, ws, dt in members]
+B = dgc.Batch(members, precision=sys.argv[2])     # outlives its graph, which reads its descriptor
+g = B.capture()
+E = dgc.Batch(copies, precision=sys.argv[2])
+for rep in range(3):
+    g.replay()
+    E.rk_step()
+    torch.cuda.synchronize()
+    assert all(torch.equal(a[1], b[1]) for a, b in zip(members, copies)), rep
+print("captured first")
+"""
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+def test_capture_as_a_process_first_step(precision):
+    """A process whose first step is the captured one replays what it steps eagerly."""
+    import os
+    import subprocess
+    import sys
+
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-u", "-c", CAPTURE_FIRST, root, precision], capture_output=True, text=True,
+                       timeout=100)
+    assert r.returncode == 0 and "captured first" in r.stdout, r.stderr[-2000:]
