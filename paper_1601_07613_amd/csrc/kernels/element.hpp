@@ -1,7 +1,9 @@
 // One SSP-RK3 stage in one pass over the elements.
 //
 // Every element evaluates its volume term, the fluxes of all its faces (a
-// face between two elements is evaluated by both, each keeping its own side)
+// face between two elements is evaluated by both, each keeping its own side:
+// the same values in f32, in f64 equal to rounding, the own trace being formed
+// with 1/sqrt(det J) and tables of the element's own)
 // and the stage combination  out = a x + b (y + dt rhs)  with y the stage
 // input; the right-hand side never leaves the registers.  Each element writes
 // only its own record, so no two work-items touch the same memory and one
@@ -458,8 +460,8 @@ __device__ __forceinline__ void element_stage(const ElemStageArgs &A, const Elem
 #pragma unroll
             for (int d = 0; d < DIM; ++d) n[d] = g[d * GP];
             const T isn = g[(DIM + 1) * GP];
-            // the flux in the face's own left-to-right sense, which both of
-            // its elements evaluate alike
+            // the flux in the face's own left-to-right sense, from both of its
+            // elements
             const T *pl = (isn < T(0) ? s_nb : s_own) + t, *pr = (isn < T(0) ? s_own : s_nb) + t;
 #pragma unroll
             for (int i = 0; i < M; ++i) {

@@ -316,3 +316,33 @@ def test_scattered_numbering_keeps_the_colored_step(gpu_device):
         assert torch.equal(a, b) == scattered
         assert torch.equal(a, c) != scattered
         assert (c - b).abs().max().item() <= 1e-14 * b.abs().max().item()
+
+
+@pytest.mark.parametrize("kind,size,p", [("periodic", 10, 1), ("periodic", 10, 3), ("periodic", 10, 5), ("quads", 12, 2),
+                                         ("quads", 12, 3), ("hybrid", 12, 2), ("tets", 4, 1), ("tets", 4, 2)])
+def test_conserved_integrals(gpu_device, kind, size, p):
+    """Both elements of a face evaluate its flux, in f64 alike to rounding: the
+    integrals over a periodic mesh stay within the rounding of 40 steps.
+
+    Bound, per stage: four roundings of every mean value in the combination,
+    and for each element's share of a face flux (|f| times at most
+    G = lambda (2 |u| + p), as a Rusanov flux is) N_p roundings of each trace,
+    N_p + Q of its projection and 40 of the flux, all of one sign."""
+    D, d, U0, Ug = _setup(kind, size, p, seed=2)
+    dt, n = 0.05 / size / (2 * p + 1), 40
+    # the integral of a variable: its mean mode times sqrt(|Omega|)
+    w = np.sqrt(d.mesh.elem_measure.astype(np.longdouble))
+    before = (w[:, None] * U0[:, :, 0]).sum(axis=0)
+    U1 = D.from_layout(_steps(D, Ug, "default", n=n, dt=dt).cpu().numpy())
+    assert np.isfinite(U1).all() and np.abs(U1 - U0).max() > 1e-6 * np.abs(U0).max()
+    after = (w[:, None] * U1[:, :, 0]).sum(axis=0)
+    u = np.abs(U0[:, :, 0] / w[:, None].astype(np.float64)).max()
+    lam, pres = 4.0, 2.0          # |v| + c < 4 and p < 2 for these states
+    G = lam * (2 * u + pres)
+    eps = np.finfo(np.float64).eps
+    shares = 2 * d.mesh.measure.sum()
+    bound = n * 3 * eps * (4 * (w[:, None] * np.abs(U0[:, :, 0])).sum(axis=0)
+                           + dt * (3 * D.n_p + D.tinfo["n_qf"] + 40) * shares * G)
+    drift = np.abs(after - before)
+    print(kind, p, "drift", drift.max(), "bound", float(bound.min()))
+    assert (drift <= bound).all(), (drift, bound)
