@@ -431,7 +431,8 @@ dgc_status dgc_surface_rhs(const dgc_dmesh *dm, const void *U, void *rhs, int32_
  * DGC_F32 evaluates both terms on the stage state rounded to f32 (the
  * colored launches through an f32 shadow) and accumulates the stages in f64.
  * ws holds the stage states and the RHS
- * (DGC_WS_RK_STEP bytes, dgc_rk_workspace_layout).  Errors: DGC_E_ARG,
+ * (DGC_WS_RK_STEP bytes, dgc_rk_workspace_layout); the one-pass stage leaves
+ * the RHS part, and for one mesh the f32 shadow, as they were.  Errors: DGC_E_ARG,
  * DGC_E_NOT_COLORED, DGC_E_WORKSPACE, DGC_E_UNSUPPORTED, DGC_E_HIP. */
 dgc_status dgc_rk_step(const dgc_dmesh *dm, double *U, double dt, int32_t variant, int32_t precision,
                        void *ws, size_t ws_bytes, void *stream);

@@ -122,12 +122,12 @@ struct ElemCfg {
     // and less LDS: 131 registers and three waves per SIMD with three sides,
     // 128 and four with two (991,232 triangles at p = 2: 226 against 219 us a
     // stage; 589,824 parallelograms at p = 2 234 with four sides, 217 with
-    // one, before the late x read below).  2D at p = 0: all sides, three of a
-    // refined triangle, whose reads are then in flight together (one at a time
-    // and in face order, as it was at first: 980,000 triangles 286 against 173
-    // us a step, the colored launches 219; 589,824 parallelograms 225, 128 and
-    // 189; 944,292 triangles of a refined mesh 295 and 235; 512 triangles 17.3
-    // and 12.4.  Tetrahedra at p = 0 are slower with all sides, 368 against 316)
+    // one; both before the late x read below, with which two sides take 116).
+    // 2D at p = 0: all sides, three of a refined triangle, whose reads are then
+    // in flight together.  One at a time, in face order / all, us a step:
+    // 980,000 triangles 286 / 173 (colored launches 219), 589,824
+    // parallelograms 225 / 128 (189), 944,292 triangles of a refined mesh 295 /
+    // 235, 512 triangles 17.3 / 12.4; tetrahedra at p = 0 (511,104) 316 / 368.
     static constexpr int FG = PROJ ? (NP >= 9 ? 1 : FS)
                               : NP == 1 && DIM == 2 ? (FS > 4 ? 3 : FS)
                               : NP == 3 && FS == 3 ? 3
@@ -139,9 +139,20 @@ struct ElemCfg {
     // empty, the test made no difference (167 us).
     static constexpr bool PADDED = FS > 4;
     // Each group's reads are issued before the work on the group ahead of it
-    // where the registers leave two or three waves either way (39,762
-    // triangles at p = 5: 85 against 93 us, 511,104 tetrahedra at p = 1: 181
-    // against 190); below, they would cost a fourth wave, which hides more.
+    // from N_p = 10 on and in 3D.  us a step with / without (registers): triangles
+    // p = 3 (145 / 127, three waves per SIMD against four) 512 elements 37.7 /
+    // 39.9, 64,800 95 / 88, 980,000 1,067 / 1,045; p = 4 (187 / 155, two against
+    // three) 66.0 / 70.4, 188 / 188, 1,998 / 1,830; p = 5 (233 / 196, two) 96 /
+    // 107, 294 / 317, 4,101 / 4,342; six slots, 37,992 and 944,292 elements: p = 3
+    // (154 / 137, three) 94 / 96, 1,337 / 1,345; p = 4 (193 / 167, two against
+    // three) 176 / 146, 2,304 / 2,140; p = 5 (244 / 208, two) 311 / 300, 4,156 /
+    // 4,013; parallelograms p = 3 (195 / 169, two) 256 elements 54 / 68, 589,824
+    // 1,243 / 1,336; mixed p = 3 (254 / 166, two against three) 308 elements 88 /
+    // 101, 191,420 728 / 730; 511,104 tetrahedra p = 0, 1, 2 (115 / 104, 138 /
+    // 130, 183 / 177: the same waves) 330 / 344, 510 / 536, 2,179 / 2,275.
+    // So small meshes gain at every order and large ones except where it costs
+    // a wave; triangles at p = 3 and 4 keep it for the small ones.  Below N_p =
+    // 10 it would cost the fourth wave.
     static constexpr bool AHEAD = NP >= 10 || M == 5;
     // the volume term by register exchanges of the team of four lanes, or
     // (M = 5) through the region, QC points at a time; through the region for
@@ -588,7 +599,7 @@ __device__ __forceinline__ void stage_elem_tables(T *s, const ElemTables &tab) {
 // Work-groups are dealt round-robin to the 8 XCDs: give each XCD runs of
 // CHUNK consecutive work-groups, whose neighbours' records then sit in its
 // own L2 (the last, incomplete round stays as it is): a stage on 991,232
-// triangles at p = 2 fetches 547 instead of 750 MB, on 511,104 tetrahedra at
+// triangles at p = 2 fetches 577 instead of 750 MB, on 511,104 tetrahedra at
 // p = 1 it takes 183 instead of 193 us.
 __device__ __forceinline__ unsigned chunked_block(unsigned b, unsigned nb) {
     constexpr unsigned CHUNK = 32;

@@ -117,14 +117,26 @@ dgc_status launch_batch(const dgc_batch::Header &h, const char *dev, int stage, 
 bool element_stage_ok(const dgc_dmesh *dm, int32_t precision) {
     const int most = dm->elem_type == DGC_TRI ? 6 : 4;
     if (!dm->elem_slots || dm->max_slots <= 0 || dm->max_slots > most) return false;
-    // f64: faster at every order, type and size measured, colored / element
-    // pass, us a step: 512 triangles p = 1 38 / 16, 996,972 triangles p = 2
-    // 1,072 / 714, 1,048,576 parallelograms p = 2 2,504 / 1,076, 1,572,864
-    // tetrahedra p = 1 2,161 / 1,669
+    // f64, ordered numberings: faster at every type and order built, from a few
+    // hundred to a million elements.  us a step, colored / element pass, smallest
+    // and largest mesh measured:
+    //   triangles, 512 and 980,000: p = 0 30 / 13, 222 / 170; p = 1 36 / 16, 545 /
+    //     372; p = 2 48 / 27, 1,067 / 610; p = 3 84 / 38, 2,068 / 1,062; p = 4 131 /
+    //     66, 4,130 / 1,996; p = 5 215 / 96, 6,869 / 3,829
+    //   refined, 2,738 and 944,220: p = 0 81 / 16, 402 / 235 to p = 5 365 / 135,
+    //     6,967 / 3,942
+    //   parallelograms, 256 and 589,824: p = 0 42 / 13, 190 / 124; p = 1 47 / 19,
+    //     489 / 262; p = 2 77 / 38, 1,473 / 606; p = 3 159 / 55, 3,262 / 1,244
+    //   mixed, 308 and 191,420: p = 0 62 / 13, 132 / 52 to p = 3 191 / 88, 1,137 / 728
+    //   tetrahedra, 384 and 511,104: p = 0 54 / 20, 506 / 309; p = 1 63 / 32, 670 /
+    //     505; p = 2 228 / 93, 3,611 / 2,170
+    // Numberings without order: element_stage_scattered.
     if (precision == DGC_F64) return true;
     // the f32 form keeps the rounding of the colored kernels (slot order =
     // color order); uniform meshes also need a face of each color per element,
-    // as the colored step that carries the volume term does
+    // as the colored step that carries the volume term does.  us a step as
+    // above: triangles p = 0 48 / 14, 238 / 133; p = 3 82 / 40, 1,745 / 1,017;
+    // parallelograms p = 3 120 / 69, 1,967 / 1,497; mixed p = 3 117 / 75, 673 / 579
     const bool mixed = dm->elem_type == DGC_MIXED;
     const int faces = dm->elem_type == DGC_TRI ? 3 : 4;
     return (mixed || (dm->max_slots == faces && dm->n_colors == faces)) &&

@@ -20,10 +20,11 @@ namespace dgc_dev {
 // interleaved so that consecutive lanes move consecutive pieces.
 // Bound by memory: two record passes, one of them scattered by record.
 // Measured into / out of the layout order: 991,232 records of 192 bytes
-// 92 / 70 us (4.1 / 5.4 TB/s), 65,522 of 320 bytes 6.7 / 7.3 us.  With one
-// 4-byte word per work-item and 64-bit index divisions 164 / 166 and
-// 14.2 / 15.0 us; with the reads under a branch per piece, which serialises
-// them, 98 / 82 and 20.2 / 20.2 us; 1, 2 or 8 pieces are within 5 % there.
+// 92 / 70 us (4.1 / 5.4 TB/s) called in a loop, 64-68 / 69-76 between the steps
+// of a solver, 65,522 of 320 bytes 6.7 / 7.3 us.  In the loop with one 4-byte
+// word per work-item and 64-bit index divisions 164 / 166 and 14.2 / 15.0 us;
+// with the reads under a branch per piece, which serialises them, 98 / 82 and
+// 20.2 / 20.2 us; 1, 2 or 8 pieces are within 5 % there.
 // Small calls, bound by latency, take one piece (the launch's comment).
 template <class V, class I, int N>
 __global__ __launch_bounds__(256) void permute_records_kernel(const V *__restrict__ src, V *__restrict__ dst,
