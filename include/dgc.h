@@ -339,7 +339,7 @@ typedef struct {
  * record, so the right-hand side is never stored and one launch covers the
  * mesh.  It needs elem_slots (it runs without them as below) and at most 6
  * face slots per triangle; in f32 it is taken where it rounds exactly as the
- * colored launches do: conforming triangles at p <= 3 and parallelograms
+ * colored launches in their default forms do: conforming triangles at p <= 3 and parallelograms
  * colored with as many colors as an element has faces, and mixed meshes.
  * It gathers an element's face and neighbour data, so large meshes at p = 0
  * and 1 whose numbering has no order (far_percent) keep the colored launches.
